@@ -5,15 +5,16 @@
 // skip concatenation; 1 644 578 parameters) maps the problem data on the node
 // grid -- log rho, log mu, log(lambda/mu), the forcing normalised by its
 // maximum, omega h and omega -- to the displacement, and its output seeds the
-// solve (x0).  Convolutions are GEMMs on MFMA over a BF16 im2col matrix
-// with FP32 accumulation; master weights, activations, gradients and Adam
-// state are FP32.  Training minimises the relative error in the M-weighted
+// solve (x0).  Convolutions are implicit GEMMs on MFMA with BF16 operands and
+// FP32 accumulation (nn_conv.hip); master weights, pre-activations, gradients
+// and Adam state are FP32.  Training minimises the relative error in the M-weighted
 // norm against solutions computed by the solver itself.
 #include <cmath>
 #include <cstring>
 #include <new>
 #include <random>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "elwh_internal.h"
@@ -43,6 +44,7 @@ const int kLayers[][3] = {
 };
 constexpr int NL = sizeof(kLayers) / sizeof(kLayers[0]);
 constexpr int NOUT = 2, NLEV = 5;
+static_assert(NL <= nn::kLayersMax, "layer tables");
 const int kWidth[NLEV] = {32, 64, 96, 128, 128};
 
 }  // namespace
@@ -52,26 +54,29 @@ struct elwh_ws {
     hipStream_t stream = nullptr;
     std::string err;
     std::vector<Conv> L;
+    char* arena = nullptr;                                // every device buffer below
+    std::vector<std::pair<void**, size_t>> want;
     int64_t nparam = 0;
     float *P = nullptr, *G = nullptr, *Mo = nullptr, *Vo = nullptr;   // params, grads, Adam moments
-    unsigned short* Pb = nullptr;                                       // BF16 copy of the params
     int step = 0;
     double out_scale = 1.0;
-    // activations
-    std::vector<float*> Z, A;          // per conv layer: pre-activation, activation
-    std::vector<float*> dA;            // per conv layer: gradient w.r.t. activation
-    float* pool[NLEV - 1] = {};        // pooled tensors (input of level l+1)
-    float* cat[NLEV - 1] = {};         // concat inputs of the decoder levels 0..3
-    float* dpool[NLEV - 1] = {};
-    float* dcat[NLEV - 1] = {};
-    float* dout = nullptr;
-    unsigned short* col = nullptr;     // im2col scratch (BF16)
-    float* dcol = nullptr;             // col2im scratch (FP32)
-    unsigned short* gbf = nullptr;     // BF16 copy of a layer's output gradient
-    float* part = nullptr;             // split-K / channel-sum partials
+    std::vector<unsigned short*> Wf, Wb;   // packed BF16 weights per layer: forward, input gradient
+    bool packed_bwd = false;               // Wb belongs to the current parameters
+    // per conv layer: pre-activation (FP32, for the gradient), activation and
+    // pre-activation gradient (BF16, the operands of the convolutions)
+    std::vector<float*> Z;
+    std::vector<unsigned short*> A, dZ;
+    unsigned short* pool[NLEV - 1] = {};   // pooled activations (input of level l+1)
+    float* dskip[NLEV - 1] = {};           // gradient of the skips, until the pooled one joins it
+    float* yout = nullptr;                 // network output
+    float* dout = nullptr;                 // its gradient
+    std::vector<float*> dbpart;            // bias-gradient partials per layer
+    float* bpart = nullptr;
+    float* part = nullptr;                 // weight-gradient partials
     int64_t part_elems = 0;
-    float* lossb = nullptr;            // per-sample loss
-    float* hloss = nullptr;            // pinned
+    float* lossb = nullptr;                // per-sample loss
+    float* lden = nullptr;                 // per-sample weighted norm of the target
+    float* hloss = nullptr;                // pinned
     // feature scratch
     double* fmax = nullptr;
     const double** dptr = nullptr;     // device pointer tables
@@ -90,12 +95,6 @@ thread_local std::string g_ws_err;
         }                                                                       \
     } while (0)
 
-// input of conv layer l given the network's buffers
-struct LayerIO {
-    const float* X;
-    int H, W;
-};
-
 int level_of(int l) {
     // e0..e4: layers 0..9 -> level l/2; d3..d0: layers 10..17 -> 3 - (l-10)/2; head: 0
     if (l < 10) return l / 2;
@@ -103,128 +102,150 @@ int level_of(int l) {
     return 0;
 }
 
-LayerIO layer_input(const elwh_ws* ws, int l, const float* x) {
+// the layer whose output is upsampled into decoder layer l
+int deeper_of(int l) { return l == 10 ? 9 : l - 1; }
+
+struct LayerIn {
+    nn::ConvSrc S;
+    int src;
+};
+
+LayerIn layer_input(const elwh_ws* ws, int l, int B, const float* x) {
     const int lev = level_of(l);
-    LayerIO io;
-    io.H = ws->H >> lev;
-    io.W = ws->W >> lev;
-    if (l == 0) io.X = x;
-    else if (l < 10 && (l % 2 == 0)) io.X = ws->pool[lev - 1];   // first conv of encoder level lev > 0
-    else if (l >= 10 && l < 18 && ((l - 10) % 2 == 0)) io.X = ws->cat[lev];
-    else io.X = ws->A[l - 1];
-    return io;
-}
-
-void conv_forward(elwh_ws* ws, int l, int B, const float* x) {
-    const Conv& c = ws->L[l];
-    const LayerIO io = layer_input(ws, l, x);
-    const int64_t M = (int64_t)B * io.H * io.W;
-    nn::im2col(ws->stream, io.X, ws->col, B, io.H, io.W, c.cin);
-    nn::gemm(ws->stream, false, false, (int)M, c.cout, 9 * c.cin, ws->col, 9 * c.cin, ws->Pb + c.woff, c.cout, ws->Z[l],
-             c.cout, 1, ws->part, 0);
-    nn::bias_act(ws->stream, ws->Z[l], ws->A[l], ws->P + c.boff, M, c.cout, c.act);
-}
-
-// dA[l] holds dL/dA on entry; accumulates dW, db; writes dX (if dX != null).
-void conv_backward(elwh_ws* ws, int l, int B, const float* x, float* dX) {
-    const Conv& c = ws->L[l];
-    const LayerIO io = layer_input(ws, l, x);
-    const int64_t M = (int64_t)B * io.H * io.W;
-    const int K = 9 * c.cin;
-    float* dZ = ws->dA[l];
-    nn::act_back(ws->stream, dZ, ws->Z[l], M * c.cout, c.act);
-    nn::channel_sum(ws->stream, dZ, M, c.cout, ws->part, 256, ws->G + c.boff, 0);
-    nn::to_bf16(ws->stream, dZ, ws->gbf, M * c.cout);
-    nn::im2col(ws->stream, io.X, ws->col, B, io.H, io.W, c.cin);
-    // dW[K][cout] = col^T dZ  (reduction over the M pixels, split for parallelism)
-    int splits = (int)std::min<int64_t>(256, std::max<int64_t>(1, M / 1024));
-    const int64_t need = (int64_t)splits * K * c.cout;
-    if (need > ws->part_elems) splits = (int)std::max<int64_t>(1, ws->part_elems / ((int64_t)K * c.cout));
-    nn::gemm(ws->stream, true, false, K, c.cout, (int)M, ws->col, K, ws->gbf, c.cout, ws->G + c.woff, c.cout, splits,
-             ws->part, 0);
-    if (dX) {
-        // dcol[M][K] = dZ W^T, then the gather back to pixels
-        nn::gemm(ws->stream, false, true, (int)M, K, c.cout, ws->gbf, c.cout, ws->Pb + c.woff, c.cout, ws->dcol, K, 1,
-                 ws->part, 0);
-        nn::col2im(ws->stream, ws->dcol, dX, B, io.H, io.W, c.cin);
+    LayerIn in;
+    in.S.B = B;
+    in.S.H = ws->H >> lev;
+    in.S.W = ws->W >> lev;
+    in.src = nn::SRC_PLAIN;
+    in.S.c0 = ws->L[l].cin;
+    if (l == 0) {
+        in.src = nn::SRC_FIRST;
+        in.S.f = x;
+    } else if (l < 10 && l % 2 == 0) {
+        in.S.x0 = ws->pool[lev - 1];   // first conv of encoder level lev > 0
+    } else if (l >= 10 && l < 18 && l % 2 == 0) {
+        in.src = nn::SRC_CAT;
+        in.S.x0 = ws->A[deeper_of(l)];
+        in.S.c0 = ws->L[deeper_of(l)].cout;
+        in.S.x1 = ws->A[2 * lev + 1];
+        in.S.c1 = kWidth[lev];
+    } else {
+        in.S.x0 = ws->A[l - 1];
     }
+    return in;
 }
 
-void forward(elwh_ws* ws, int B, const float* x) {
-    const int H = ws->H, W = ws->W;
-    for (int lev = 0; lev < NLEV; ++lev) {
-        conv_forward(ws, 2 * lev, B, x);
-        conv_forward(ws, 2 * lev + 1, B, x);
-        if (lev < NLEV - 1)
-            nn::avgpool(ws->stream, ws->A[2 * lev + 1], ws->pool[lev], B, H >> lev, W >> lev, kWidth[lev]);
+// Pre-activations are kept only when a backward pass follows.
+elwh_status forward(elwh_ws* ws, int B, const float* x, float* y, bool keep) {
+    // encoder, then decoder level 3 down to 0, then the head: the layer order
+    for (int l = 0; l < NL; ++l) {
+        const Conv& c = ws->L[l];
+        const LayerIn in = layer_input(ws, l, B, x);
+        const bool head = l == NL - 1;
+        unsigned short* pool = l < 8 && l % 2 == 1 ? ws->pool[l / 2] : nullptr;
+        WCK(nn::conv_forward(ws->stream, in.S, in.src, c.cin, c.cout, c.act, ws->Wf[l], ws->P + c.boff,
+                             keep ? ws->Z[l] : nullptr, ws->A[l], pool, head ? y : nullptr));
     }
-    // decoder: level 3 down to 0
-    for (int lev = NLEV - 2; lev >= 0; --lev) {
-        const int deeper = lev == NLEV - 2 ? 9 : 10 + 2 * (NLEV - 3 - lev) + 1;   // last conv of the level below
-        const int cup = ws->L[deeper].cout;
-        const int cskip = kWidth[lev];
-        const int Hl = H >> lev, Wl = W >> lev;
-        nn::upsample(ws->stream, ws->A[deeper], ws->cat[lev], B, Hl / 2, Wl / 2, cup, cup + cskip, 0);
-        nn::copy_channels(ws->stream, ws->A[2 * lev + 1], cskip, 0, ws->cat[lev], cup + cskip, cup,
-                          (int64_t)B * Hl * Wl, cskip, 0);
-        const int la = 10 + 2 * (NLEV - 2 - lev);
-        conv_forward(ws, la, B, x);
-        conv_forward(ws, la + 1, B, x);
-    }
-    conv_forward(ws, NL - 1, B, x);
+    return ELWH_OK;
 }
 
-void backward(elwh_ws* ws, int B, const float* x) {
-    const int H = ws->H, W = ws->W;
-    // head: dA[head] = dout
-    (void)hipMemcpyAsync(ws->dA[NL - 1], ws->dout, sizeof(float) * (size_t)B * H * W * NOUT, hipMemcpyDeviceToDevice,
-                         ws->stream);
-    conv_backward(ws, NL - 1, B, x, ws->dA[NL - 2]);
+// BF16 weights of the current parameters in the kernels' layout; those of the
+// input gradient (none for the first layer) when a backward pass needs them.
+void pack(elwh_ws* ws, bool backward) {
+    nn::PackTable T;
+    T.backward = backward ? 1 : 0;
+    int n = 0;
+    for (int l = backward ? 1 : 0; l < NL; ++l) {
+        const Conv& c = ws->L[l];
+        T.l[n++] = {backward ? ws->Wb[l] : ws->Wf[l], c.woff, c.cin, c.cout, nn::pack_ksteps(c.cin, c.cout, backward)};
+    }
+    nn::pack_weights(ws->stream, T, n, ws->P);
+    if (!backward) ws->packed_bwd = false;
+}
+
+// Gradients of every parameter into G; dout holds dL/dy and dbpart[head] its sums.
+elwh_status backward(elwh_ws* ws, int B, const float* x) {
+    if (!ws->packed_bwd) {
+        pack(ws, true);
+        ws->packed_bwd = true;
+    }
+    nn::BiasGrads T;
+    auto bias_layer = [&](int l, int64_t rows) {
+        T.l[l] = {ws->dbpart[l], ws->G + ws->L[l].boff, rows, ws->L[l].cout};
+    };
+    bias_layer(NL - 1, nn::loss_blocks((int64_t)B * ws->H * ws->W));
+    auto back = [&](int l) -> elwh_status {
+        const Conv& c = ws->L[l];
+        const LayerIn in = layer_input(ws, l, B, x);
+        const bool head = l == NL - 1;
+        nn::ConvSrc gz;
+        gz.B = B;
+        gz.H = in.S.H;
+        gz.W = in.S.W;
+        gz.c0 = c.cout;
+        gz.x0 = head ? nullptr : ws->dZ[l];
+        gz.f = head ? ws->dout : nullptr;
+        const int srcz = head ? nn::SRC_HEAD : nn::SRC_PLAIN;
+        WCK(nn::conv_weight_grad(ws->stream, in.S, in.src, gz, srcz, c.cin, c.cout, ws->part, ws->part_elems,
+                                 ws->G + c.woff));
+        if (l == 0) return ELWH_OK;
+        nn::GradDst D;
+        int to = l - 1;   // the layer that produced this input
+        if (in.src == nn::SRC_CAT) {
+            D.mode = nn::GRAD_CAT;
+            to = deeper_of(l);
+            D.cup = ws->L[to].cout;
+            D.dskip = ws->dskip[level_of(l)];
+        } else if (l < 10 && l % 2 == 0) {
+            D.mode = nn::GRAD_UNPOOL;
+            D.dskip = ws->dskip[level_of(l) - 1];
+        }
+        D.Z = ws->Z[to];
+        D.dZ = ws->dZ[to];
+        D.dbpart = ws->dbpart[to];
+        WCK(nn::conv_input_grad(ws->stream, gz, srcz, c.cout, c.cin, ws->Wb[l], D));
+        bias_layer(to, nn::grad_rows(c.cin, B, gz.H, gz.W));
+        return ELWH_OK;
+    };
+    elwh_status st;
+    if ((st = back(NL - 1))) return st;
     for (int lev = 0; lev <= NLEV - 2; ++lev) {
         const int la = 10 + 2 * (NLEV - 2 - lev);
-        const int deeper = lev == NLEV - 2 ? 9 : la - 1;
-        const int cup = ws->L[deeper].cout;
-        const int cskip = kWidth[lev];
-        const int Hl = H >> lev, Wl = W >> lev;
-        conv_backward(ws, la + 1, B, x, ws->dA[la]);
-        conv_backward(ws, la, B, x, ws->dcat[lev]);
-        nn::upsample_back(ws->stream, ws->dcat[lev], ws->dA[deeper], B, Hl / 2, Wl / 2, cup, cup + cskip, 0);
-        nn::copy_channels(ws->stream, ws->dcat[lev], cup + cskip, cup, ws->dA[2 * lev + 1], cskip, 0,
-                          (int64_t)B * Hl * Wl, cskip, 0);
+        if ((st = back(la + 1)) || (st = back(la))) return st;
     }
-    // encoder, deepest first; each level's input gradient flows back through the pooling
-    for (int lev = NLEV - 1; lev >= 0; --lev) {
-        conv_backward(ws, 2 * lev + 1, B, x, ws->dA[2 * lev]);
-        if (lev == 0) {
-            conv_backward(ws, 0, B, x, nullptr);
-        } else {
-            conv_backward(ws, 2 * lev, B, x, ws->dpool[lev - 1]);
-            nn::avgpool_back(ws->stream, ws->dpool[lev - 1], ws->dA[2 * lev - 1], B, H >> (lev - 1), W >> (lev - 1),
-                             kWidth[lev - 1], 1);
-        }
-    }
+    // encoder, deepest first
+    for (int l = 9; l >= 0; --l)
+        if ((st = back(l))) return st;
+    nn::bias_grads(ws->stream, T, NL, ws->bpart);
+    return ELWH_OK;
 }
 
-elwh_status alloc(elwh_ws* ws, void** p, size_t bytes) {
-    if (hipMalloc(p, bytes) != hipSuccess) {
-        *p = nullptr;
-        ws->err = "device allocation failed (" + std::to_string(bytes) + " bytes)";
+// Every device buffer is a part of one allocation: alloc() notes the pointer and
+// its size, commit() allocates the sum and hands out the parts (creating the
+// handle with one hipMalloc per buffer spent longer on those calls than on
+// anything else).
+void alloc(elwh_ws* ws, void** p, size_t bytes) { ws->want.emplace_back(p, (bytes + 255) / 256 * 256); }
+
+elwh_status commit(elwh_ws* ws) {
+    size_t total = 0;
+    for (const auto& w : ws->want) total += w.second;
+    if (hipMalloc(reinterpret_cast<void**>(&ws->arena), total) != hipSuccess) {
+        ws->arena = nullptr;
+        ws->err = "device allocation failed (" + std::to_string(total) + " bytes)";
         return ELWH_ERR_ALLOC;
     }
-    (void)hipMemsetAsync(*p, 0, bytes, ws->stream);
+    (void)hipMemsetAsync(ws->arena, 0, total, ws->stream);
+    size_t off = 0;
+    for (const auto& w : ws->want) {
+        *w.first = ws->arena + off;
+        off += w.second;
+    }
+    ws->want.clear();
     return ELWH_OK;
 }
 
 void free_ws(elwh_ws* ws) {
-    auto f = [](void* p) {
-        if (p) (void)hipFree(p);
-    };
-    f(ws->P); f(ws->G); f(ws->Mo); f(ws->Vo); f(ws->Pb);
-    for (auto* p : ws->Z) f(p);
-    for (auto* p : ws->A) f(p);
-    for (auto* p : ws->dA) f(p);
-    for (int k = 0; k < NLEV - 1; ++k) { f(ws->pool[k]); f(ws->cat[k]); f(ws->dpool[k]); f(ws->dcat[k]); }
-    f(ws->dout); f(ws->col); f(ws->dcol); f(ws->gbf); f(ws->part); f(ws->lossb); f(ws->fmax); f(ws->dptr);
+    if (ws->arena) (void)hipFree(ws->arena);
     if (ws->hloss) (void)hipHostFree(ws->hloss);
 }
 
@@ -390,46 +411,52 @@ elwh_status elwh_ws_create(int max_batch, int H, int W, unsigned long long seed,
         ws->L.push_back(c);
     }
     ws->nparam = off;
-    elwh_status st;
     const size_t np = (size_t)off;
-    if ((st = alloc(ws, (void**)&ws->P, np * 4)) || (st = alloc(ws, (void**)&ws->G, np * 4)) ||
-        (st = alloc(ws, (void**)&ws->Mo, np * 4)) || (st = alloc(ws, (void**)&ws->Vo, np * 4)) ||
-        (st = alloc(ws, (void**)&ws->Pb, np * 2)))
-        return fail(st);
+    for (float** p : {&ws->P, &ws->G, &ws->Mo, &ws->Vo}) alloc(ws, (void**)p, np * 4);
     const int64_t B = max_batch;
-    int64_t max_col = 0, max_act = 0;
+    for (auto* v : {&ws->Wf, &ws->Wb, &ws->A, &ws->dZ}) v->resize(NL);
     ws->Z.resize(NL);
-    ws->A.resize(NL);
-    ws->dA.resize(NL);
+    ws->dbpart.resize(NL);
+    int64_t max_w = 0;
     for (int l = 0; l < NL; ++l) {
+        const Conv& c = ws->L[l];
         const int lev = level_of(l);
         const int64_t npix = B * (H >> lev) * (W >> lev);
-        const size_t bytes = (size_t)npix * ws->L[l].cout * 4;
-        if ((st = alloc(ws, (void**)&ws->Z[l], bytes)) || (st = alloc(ws, (void**)&ws->A[l], bytes)) ||
-            (st = alloc(ws, (void**)&ws->dA[l], bytes)))
-            return fail(st);
-        max_col = std::max(max_col, npix * 9 * ws->L[l].cin);
-        max_act = std::max(max_act, npix * ws->L[l].cout);
+        alloc(ws, (void**)&ws->Wf[l], nn::packed_elems(c.cin, c.cout, false) * 2);
+        if (l > 0) alloc(ws, (void**)&ws->Wb[l], nn::packed_elems(c.cin, c.cout, true) * 2);
+        max_w = std::max<int64_t>(max_w, 9LL * c.cin * c.cout);
+        if (l < NL - 1) {
+            alloc(ws, (void**)&ws->Z[l], (size_t)npix * c.cout * 4);
+            alloc(ws, (void**)&ws->A[l], (size_t)npix * c.cout * 2);
+            alloc(ws, (void**)&ws->dZ[l], (size_t)npix * c.cout * 2);
+        }
+        // bias partials: the rows written by the layer whose input gradient
+        // reaches this layer through its SiLU
+        int64_t rows = nn::loss_blocks(npix);
+        if (l < NL - 1) {
+            const int by = l + 1, lb = level_of(by);
+            rows = nn::grad_rows(kLayers[by][0], max_batch, H >> lb, W >> lb);
+        }
+        alloc(ws, (void**)&ws->dbpart[l], (size_t)rows * c.cout * 4);
     }
     for (int lev = 0; lev < NLEV - 1; ++lev) {
         const int64_t npix1 = B * (H >> (lev + 1)) * (W >> (lev + 1));
         const int64_t npix = B * (H >> lev) * (W >> lev);
-        const int ccat = kWidth[lev] + (lev == NLEV - 2 ? kWidth[NLEV - 1] : kWidth[lev + 1]);
-        if ((st = alloc(ws, (void**)&ws->pool[lev], (size_t)npix1 * kWidth[lev] * 4)) ||
-            (st = alloc(ws, (void**)&ws->dpool[lev], (size_t)npix1 * kWidth[lev] * 4)) ||
-            (st = alloc(ws, (void**)&ws->cat[lev], (size_t)npix * ccat * 4)) ||
-            (st = alloc(ws, (void**)&ws->dcat[lev], (size_t)npix * ccat * 4)))
-            return fail(st);
+        alloc(ws, (void**)&ws->pool[lev], (size_t)npix1 * kWidth[lev] * 2);
+        alloc(ws, (void**)&ws->dskip[lev], (size_t)npix * kWidth[lev] * 4);
     }
-    ws->part_elems = std::max<int64_t>(std::max<int64_t>(max_act, 256LL * 256), 256LL * 9 * 256 * 128);
-    if ((st = alloc(ws, (void**)&ws->dout, (size_t)B * H * W * NOUT * 4)) ||
-        (st = alloc(ws, (void**)&ws->col, (size_t)max_col * 2)) ||
-        (st = alloc(ws, (void**)&ws->dcol, (size_t)max_col * 4)) ||
-        (st = alloc(ws, (void**)&ws->gbf, (size_t)max_act * 2)) ||
-        (st = alloc(ws, (void**)&ws->part, (size_t)ws->part_elems * 4)) ||
-        (st = alloc(ws, (void**)&ws->lossb, (size_t)B * 4)) || (st = alloc(ws, (void**)&ws->fmax, (size_t)B * 8)) ||
-        (st = alloc(ws, (void**)&ws->dptr, (size_t)B * 8 * sizeof(double*))))
-        return fail(st);
+    // weight-gradient shares: about 512 workgroups of one 32 x 32 channel block each
+    ws->part_elems = std::max<int64_t>(512LL * 9 * 32 * 32, max_w);
+    alloc(ws, (void**)&ws->dout, (size_t)B * H * W * NOUT * 4);
+    alloc(ws, (void**)&ws->yout, (size_t)B * H * W * NOUT * 4);
+    alloc(ws, (void**)&ws->bpart, sizeof(float) * nn::kLayersMax * nn::kBiasChunks * 128);
+    alloc(ws, (void**)&ws->part, (size_t)ws->part_elems * 4);
+    alloc(ws, (void**)&ws->lossb, (size_t)B * 4);
+    alloc(ws, (void**)&ws->lden, (size_t)B * 4);
+    alloc(ws, (void**)&ws->fmax, (size_t)B * 8);
+    alloc(ws, (void**)&ws->dptr, (size_t)B * 8 * sizeof(double*));
+    elwh_status st;
+    if ((st = commit(ws))) return fail(st);
     if (hipHostMalloc((void**)&ws->hloss, (size_t)B * 4, hipHostMallocDefault) != hipSuccess) return fail(ELWH_ERR_ALLOC);
     // He-style initialisation (seeded), zero biases; the head starts small
     std::vector<float> hp(np, 0.f);
@@ -442,7 +469,7 @@ elwh_status elwh_ws_create(int max_batch, int H, int W, unsigned long long seed,
     }
     if (hipMemcpyAsync(ws->P, hp.data(), np * 4, hipMemcpyHostToDevice, ws->stream) != hipSuccess)
         return fail(ELWH_ERR_HIP);
-    nn::to_bf16(ws->stream, ws->P, ws->Pb, ws->nparam);
+    pack(ws, false);
     if (hipStreamSynchronize(ws->stream) != hipSuccess) return fail(ELWH_ERR_HIP);
     *out = ws;
     return ELWH_OK;
@@ -463,7 +490,7 @@ elwh_status elwh_ws_params(elwh_ws* ws, float* get, const float* set, double* ou
     if (!ws) return ELWH_ERR_ARG;
     if (set) {
         WCK(hipMemcpyAsync(ws->P, set, ws->nparam * 4, hipMemcpyHostToDevice, ws->stream));
-        nn::to_bf16(ws->stream, ws->P, ws->Pb, ws->nparam);
+        pack(ws, false);
         WCK(hipMemsetAsync(ws->Mo, 0, ws->nparam * 4, ws->stream));
         WCK(hipMemsetAsync(ws->Vo, 0, ws->nparam * 4, ws->stream));
         ws->step = 0;
@@ -477,9 +504,8 @@ elwh_status elwh_ws_params(elwh_ws* ws, float* get, const float* set, double* ou
 
 elwh_status elwh_ws_forward(elwh_ws* ws, int B, const float* x, float* y) {
     if (!ws || !x || !y || B < 1 || B > ws->maxB) return ELWH_ERR_ARG;
-    forward(ws, B, x);
-    WCK(hipMemcpyAsync(y, ws->A[NL - 1], sizeof(float) * (size_t)B * ws->H * ws->W * NOUT, hipMemcpyDeviceToDevice,
-                       ws->stream));
+    elwh_status st;
+    if ((st = forward(ws, B, x, y, false))) return st;
     WCK(hipGetLastError());
     return ELWH_OK;
 }
@@ -487,9 +513,10 @@ elwh_status elwh_ws_forward(elwh_ws* ws, int B, const float* x, float* y) {
 elwh_status elwh_ws_loss_grad(elwh_ws* ws, int B, const float* x, const float* y, const float* w, float* loss,
                               float* grad_host) {
     if (!ws || !x || !y || !w || B < 1 || B > ws->maxB) return ELWH_ERR_ARG;
-    forward(ws, B, x);
-    nn::loss(ws->stream, ws->A[NL - 1], y, w, B, (int64_t)ws->H * ws->W, NOUT, ws->dout, ws->lossb);
-    backward(ws, B, x);
+    elwh_status st;
+    if ((st = forward(ws, B, x, ws->yout, true))) return st;
+    nn::loss(ws->stream, ws->yout, y, w, B, (int64_t)ws->H * ws->W, ws->dout, ws->lossb, ws->lden, ws->dbpart[NL - 1]);
+    if ((st = backward(ws, B, x))) return st;
     WCK(hipMemcpyAsync(ws->hloss, ws->lossb, sizeof(float) * B, hipMemcpyDeviceToHost, ws->stream));
     if (grad_host) WCK(hipMemcpyAsync(grad_host, ws->G, ws->nparam * 4, hipMemcpyDeviceToHost, ws->stream));
     WCK(hipStreamSynchronize(ws->stream));
@@ -504,12 +531,13 @@ elwh_status elwh_ws_loss_grad(elwh_ws* ws, int B, const float* x, const float* y
 elwh_status elwh_ws_train_step(elwh_ws* ws, int B, const float* x, const float* y, const float* w, float lr,
                                float* loss) {
     if (!ws || !x || !y || !w || B < 1 || B > ws->maxB || !(lr > 0)) return ELWH_ERR_ARG;
-    forward(ws, B, x);
-    nn::loss(ws->stream, ws->A[NL - 1], y, w, B, (int64_t)ws->H * ws->W, NOUT, ws->dout, ws->lossb);
-    backward(ws, B, x);
+    elwh_status st;
+    if ((st = forward(ws, B, x, ws->yout, true))) return st;
+    nn::loss(ws->stream, ws->yout, y, w, B, (int64_t)ws->H * ws->W, ws->dout, ws->lossb, ws->lden, ws->dbpart[NL - 1]);
+    if ((st = backward(ws, B, x))) return st;
     ws->step++;
     nn::adam(ws->stream, ws->P, ws->G, ws->Mo, ws->Vo, ws->nparam, lr, 0.9f, 0.999f, 1e-8f, ws->step);
-    nn::to_bf16(ws->stream, ws->P, ws->Pb, ws->nparam);
+    pack(ws, false);
     if (loss) {
         WCK(hipMemcpyAsync(ws->hloss, ws->lossb, sizeof(float) * B, hipMemcpyDeviceToHost, ws->stream));
         WCK(hipStreamSynchronize(ws->stream));
@@ -566,8 +594,8 @@ elwh_status elwh_ws_normalize(elwh_ws* ws, int B, float* y, const float* w) {
 elwh_status elwh_ws_predict(elwh_ws* ws, int B, int n, const float* x, const double* const* f, const double* omega_dev,
                             double* const* x0) {
     if (!ws || B < 1 || B > ws->maxB || n != ws->H || !x || !f || !omega_dev || !x0) return ELWH_ERR_ARG;
-    forward(ws, B, x);
     elwh_status st;
+    if ((st = forward(ws, B, x, ws->yout, false))) return st;
     if ((st = upload_ptrs(ws, B, f, 3)) ||
         (st = upload_ptrs(ws, B, reinterpret_cast<const double* const*>(x0), 5)))
         return st;
@@ -575,7 +603,7 @@ elwh_status elwh_ws_predict(elwh_ws* ws, int B, int n, const float* x, const dou
     const int M = ws->maxB;
     hipLaunchKernelGGL(fmax_kernel, dim3(B), dim3(256), 0, ws->stream, d + 3 * M, (n + 1) * (n + 1), ws->fmax);
     hipLaunchKernelGGL(to_field_kernel, dim3(g1((int64_t)B * (n + 1) * (n + 1))), dim3(256), 0, ws->stream,
-                       ws->A[NL - 1], omega_dev, ws->fmax, ws->out_scale, n,
+                       ws->yout, omega_dev, ws->fmax, ws->out_scale, n,
                        reinterpret_cast<double* const*>(const_cast<double**>(d + 5 * M)), B);
     WCK(hipStreamSynchronize(ws->stream));
     WCK(hipGetLastError());

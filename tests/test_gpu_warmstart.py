@@ -184,3 +184,41 @@ def test_trained_network_start_vs_zero_start(E):
         assert i["relres_fp64"] <= 1e-8
         assert a <= b + 2
     net.close()
+
+
+def _bf16(a):
+    """Round to BF16 (nearest even), back in float64."""
+    u = np.ascontiguousarray(a, dtype=np.float32).view(np.uint32)
+    u = (u + 0x7FFF + ((u >> 16) & 1)) & np.uint32(0xFFFF0000)
+    return u.view(np.float32).astype(np.float64)
+
+
+@pytest.mark.parametrize("B,H,W", [(1, 16, 16), (3, 16, 48), (2, 48, 16), (1, 80, 112), (1, 32, 272)])
+def test_convolution_tiles(E, monkeypatch, B, H, W):
+    """Image sizes at the edges of the convolution tiles (rows of 32 or 16
+    pixels, levels down to one pixel, widths that are no multiple of the tile)
+    against the oracle network with BF16-rounded operands.  Forward: only FP32
+    sums differ; one that lands on another BF16 value moves by 2^-8, at a rate
+    of about 1e-6 / 2^-8, over 19 layers about 3e-4: within 2e-3.  Gradient:
+    the oracle keeps its output gradients unrounded, up to 19 roundings of rms
+    1.1e-3 in quadrature, twice that for their growth: within 2e-2 per layer."""
+    rng = np.random.default_rng(H * W + B)
+    theta = _setup(11, 1, 16)[0]
+    x = rng.standard_normal((B, H, W, 7)).astype(np.float32)
+    y = rng.standard_normal((B, H, W, 2)).astype(np.float32)
+    w = rng.uniform(0.5, 1.5, (B, H, W)).astype(np.float32)
+    im2col, unpack = unet.im2col, unet.unpack
+    monkeypatch.setattr(unet, "im2col", lambda X: _bf16(im2col(X)))
+    monkeypatch.setattr(unet, "unpack", lambda t: [(_bf16(Wl), b) for Wl, b in unpack(t)])
+    _, gr, yr = unet.loss_and_grad(theta, x.astype(np.float64), y.astype(np.float64), w.astype(np.float64))
+    net = E.WarmStartNet(B, H, W)
+    net.set_params(theta)
+    yh = net.forward(_t(x)).cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(yh - yr) <= 2e-3 * np.linalg.norm(yr)
+    _, g = net.loss_grad(_t(x), _t(y), _t(w))
+    off = 0
+    for k, (ci, co, _) in enumerate(unet.LAYERS):
+        for n in (9 * ci * co, co):
+            a, b = g[off:off + n], gr[off:off + n]
+            assert np.linalg.norm(a - b) <= 2e-2 * np.linalg.norm(b), (k, n)
+            off += n
