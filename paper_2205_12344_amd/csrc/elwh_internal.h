@@ -68,6 +68,33 @@ struct Args2D {
     int final_;
 };
 
+// Register tiles of a 2-D grid (kernels2d_tile.hip): NW wavefronts of R rows of
+// 64 columns, up to H steps per launch (0: the marching kernels are used).
+constexpr int kTileMaxSteps = 12;
+struct TileShape {
+    int NW = 0, R = 0, H = 0;
+};
+struct Tile2D {
+    int nx, ny;
+    int64_t P, CS;
+    int jlo, jhi, free_lo, free_hi;
+    double cxx2, cyy2, cxy;
+    int H, steps, first;      // halo, steps of this launch, whether it starts the application
+    double w0;                // weight of u^0 (first launch)
+    double wk[kTileMaxSteps], fck[kTileMaxSteps];   // per step: weight of the new level, forcing factor of the current one
+};
+
+// The second field of a register-tile launch: velocity accumulator and its A_h
+// base, damping tables, and which x faces are unknown columns.
+struct TwoField2D {
+    const double* base1;
+    double* acc1;
+    const double *dmp, *dmpx;
+    int imp_lo, imp_hi, xfree_lo, xfree_hi;
+    double w0v, dtw;          // weight of the second field, dt times its scale (first launch)
+    double wvk[kTileMaxSteps];   // per step: weight of the current level's centred velocity
+};
+
 // Two-field step on a 2-D grid with impedance y faces (kernels2d_damped.hip).
 struct Damp2D {
     Args2D A;                 // geometry, stencil constants, w (of u^{n+1}), w0 (of u^0), fc
@@ -168,6 +195,7 @@ struct elwh_ctx {
 
     // tiling of the fused step kernels (set by elwh_set_tile / elwh_autotune)
     elwh::Tile tile64, tile32;
+    bool tile64_set = false;           // the FP64 tiling was asked for: no register tiles
 
     // kernel profiling: three events per filter application (start, after the
     // half step, after the last step) on the context's stream
@@ -256,6 +284,13 @@ template <typename T>
 void launch_step3d_k2(int RB, int TZ, bool force, bool comp, hipStream_t s, const T* u, const T* uprev, T* outA,
                       T* outB, double* acc, float* acclo, const T* ca, const T* cl, const T* cm, const T* f,
                       const Args3D& A);
+// The register-tile shape an FP64 application (one-field, or two-field) of a 2-D
+// Cartesian context takes (H = 0: none, the marching kernels), and such an
+// application.
+TileShape tile2d_shape(const elwh_ctx* c, bool two);
+void run_filter_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool with_force, bool amode, double* out);
+void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x0, const double* z1, bool with_force,
+                                bool amode, double s_in, double s_out, double* out0, double* out1);
 bool tile_valid_curv(bool fp32, int V, int TY);
 bool tile_valid_curv3(bool fp32, int V, int TY);
 // One filter application on a mapped 2-D grid (kernels2d_curv.hip).

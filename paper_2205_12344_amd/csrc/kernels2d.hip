@@ -456,6 +456,11 @@ static void run_steps_2d(elwh_ctx* c, Args2D A, int nrows, Tile t, bool with_for
 }
 
 void run_filter_2d(elwh_ctx* c, const double* x, bool with_force, bool amode, bool fp32, double* out) {
+    const TileShape ts = fp32 ? TileShape() : tile2d_shape(c, false);
+    if (ts.H > 0) {
+        run_filter_tile2d(c, ts, x, with_force, amode, out);
+        return;
+    }
     hipStream_t s = c->stream;
     Args2D A = make_args2d(c);
     const int nrows = A.jhi - A.jlo + 1;

@@ -1,0 +1,487 @@
+// 2-D El-WaveHoltz steps on tiles that stay in registers, for grids too small
+// to fill the chip with marching wavefronts (FP64).
+//
+// The marching kernels (kernels2d_multi.hip) walk a strip row by row, one row's
+// latency after the other; with K = 4 steps per launch a wavefront spends about
+// 1.5 us per row, so a grid of 64 or 256 rows takes 16 us for four steps however
+// few wavefronts it needs.  Here a workgroup owns a tile of NW R rows x 64
+// columns, wavefront w its rows w R .. w R + R - 1, one column per lane: state,
+// accumulator and the stencil coefficients of every node stay in registers for
+// all the steps of a launch, and after each step the wavefronts exchange their
+// first and last rows through LDS (two buffers, one barrier per step); x
+// neighbours come by DPP.  A launch of up to H steps computes the tile's inner
+// (64 - 2 H) x (NW R - 2 H) nodes exactly (the outer ones are recomputed by the
+// neighbouring tiles) and needs u^n and u^{n-1} on the whole tile, so more steps
+// per launch cost redundant arithmetic and save launches and loads.
+//
+// The coefficients are formed once per launch with a = c dt^2 / rho, the
+// metric factors and the boundary closure folded in: 16 per node, and a
+// step of one node is 16 differences and 16 fused multiply-adds.  A node that
+// is no unknown has zero coefficients and keeps its zero.  A traction-free
+// face is the interior stencil with a ghost row (or column) equal to the face's
+// own, the face normal's compact and mixed terms doubled and the coefficient of
+// the one-sided difference's own node negated; the ghost is the value itself.
+//
+// Two fields (absorbing faces): any face may be an unknown one, so the ghost
+// also exists per column (a select on the lanes of the face, in tiles that
+// touch it); face nodes are damped, u^{n+1} <- (u^{n+1} + g u^{n-1}) / (1 + g)
+// with g and the reciprocal in LDS, and the centred velocity of every level is
+// added to a second accumulator.
+//
+// The launch that starts an application takes the even-in-time start u^1 = u^0
+// + (a/2)(Ltilde u^0 - f) (with a second field, + dt (1 - g) u1) as its first step.
+#include <algorithm>
+#include <type_traits>
+#include <cstdio>
+#include <cstdlib>
+
+#include "step2d_common.h"
+
+namespace elwh {
+
+namespace {
+
+// Differences and products of one component's row: the eight stencil terms.
+struct Coef {
+    double xL, xR, yS, yN;   // compact terms (own component): edges to the left, right, below, above
+    double cL, cR;           // mixed terms: vertical differences of the other component, left and right column
+    double cS, cN;           // mixed terms: horizontal differences of the other component, row below and above
+};
+
+__device__ __forceinline__ double stencil_row(const Coef& q, double C, double L, double R, double S, double N,
+                                              double oSL, double oSR, double oNL, double oNR) {
+    double s = q.xR * (R - C);
+    s = fma(-q.xL, C - L, s);
+    s = fma(q.yN, N - C, s);
+    s = fma(-q.yS, C - S, s);
+    s = fma(q.cR, oNR - oSR, s);
+    s = fma(-q.cL, oNL - oSL, s);
+    s = fma(q.cN, oNR - oNL, s);
+    return fma(-q.cS, oSR - oSL, s);
+}
+
+template <int NW, int R, bool FORCE, bool TWO>
+__global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restrict__ u, const double* __restrict__ uprev,
+                                                         double* __restrict__ outA, double* __restrict__ outB,
+                                                         const double* __restrict__ base, double* __restrict__ acc,
+                                                         const double* __restrict__ ca, const double* __restrict__ cl,
+                                                         const double* __restrict__ cm, const double* __restrict__ f,
+                                                         Tile2D A, TwoField2D D) {
+    __shared__ double ex[2][NW][2][2][64];   // [buffer][wavefront][first, last row][u, v][column]
+    // damping of the tile's face nodes: g, 1 / (1 + g) of u, then of v
+    __shared__ double dg[TWO ? NW * R : 1][4][64];
+    const int ilo = TWO && D.xfree_lo ? 0 : 1, ihi = TWO && D.xfree_hi ? A.nx : A.nx - 1;   // unknown columns
+    const int ntx = (ihi - ilo + 64 - 2 * A.H) / (64 - 2 * A.H);
+    const int HV = NW * R - 2 * A.H, nty = (A.jhi - A.jlo + HV) / HV;
+    int t;
+    if (!xcd_tile((int)blockIdx.x, ntx * nty, t)) return;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: scalar row indices)
+    const int col = ilo + (t % ntx) * (64 - 2 * A.H) - A.H + lane;
+    const int row0 = A.jlo + (t / ntx) * HV - A.H + w * R;   // first row of this wavefront
+    const bool colv = col >= 0 && col <= A.nx, colu = col >= ilo && col <= ihi;
+    const int64_t P = A.P, CS = A.CS;
+
+    // rows 0 and R + 1 of these arrays are the neighbours' (row r = grid row row0 + r - 1)
+    double u0[R + 2], v0[R + 2], u1[R + 2], v1[R + 2], au[R], av[R], fu[R], fv[R], bu[R], bv[R];
+    const bool xlo = TWO && D.xfree_lo && col == 0, xhi = TWO && D.xfree_hi && col == A.nx;
+    bool damped = false;   // (uniform) this wavefront has nodes of an impedance face
+    Coef qu[R], qv[R];
+    {
+        double l[R + 2], m[R + 2], a[R];
+#pragma unroll
+        for (int r = 0; r < R + 2; ++r) {
+            const int j = row0 + r - 1;
+            const bool in = colv && j >= 0 && j <= A.ny;
+            const int64_t o = (int64_t)j * P + col;
+            l[r] = in ? cl[o] : 0.0;
+            m[r] = in ? cm[o] : 0.0;
+            u0[r] = in ? u[o] : 0.0;
+            v0[r] = in ? u[o + CS] : 0.0;
+            if (r >= 1 && r <= R) {
+                const bool unk = colu && j >= A.jlo && j <= A.jhi;
+                a[r - 1] = unk ? ca[o] : 0.0;
+                u1[r] = unk && uprev ? uprev[o] : 0.0;
+                v1[r] = unk && uprev ? uprev[o + CS] : 0.0;
+                const int q = w * R + r - 1;
+                const bool own = unk && lane >= A.H && lane < 64 - A.H && q >= A.H && q < NW * R - A.H;
+                const double* b = A.first ? base : acc;
+                au[r - 1] = own && b ? b[o] : 0.0;
+                av[r - 1] = own && b ? b[o + CS] : 0.0;
+                if constexpr (TWO) {
+                    const double* b1 = A.first ? D.base1 : D.acc1;
+                    bu[r - 1] = own && b1 ? b1[o] : 0.0;
+                    bv[r - 1] = own && b1 ? b1[o + CS] : 0.0;
+                    double gu = 0.0, gv = 0.0;
+                    if (unk && ((D.imp_lo && j == 0) || (D.imp_hi && j == A.ny))) {
+                        const double* g = D.dmp + (j == 0 ? 0 : 2) * P + col;
+                        gu += g[0];
+                        gv += g[P];
+                    }
+                    if (unk && (xlo || xhi)) {
+                        const double* g = D.dmpx + (xlo ? 0 : 2) * (A.ny + 1) + j;
+                        gu += g[0];
+                        gv += g[A.ny + 1];
+                    }
+                    dg[q][0][lane] = gu;
+                    dg[q][1][lane] = 1.0 / (1.0 + gu);
+                    dg[q][2][lane] = gv;
+                    dg[q][3][lane] = 1.0 / (1.0 + gv);
+                    damped |= __any(gu != 0.0 || gv != 0.0);
+                }
+                fu[r - 1] = FORCE && unk ? ca[o] * f[o] : 0.0;
+                fv[r - 1] = FORCE && unk ? ca[o] * f[o + CS] : 0.0;
+            }
+        }
+        u1[0] = u1[R + 1] = v1[0] = v1[R + 1] = 0.0;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int j = row0 + k, r = k + 1;
+            const bool top = A.free_hi && j == A.ny, bot = A.free_lo && j == 0;
+            const double lL = lane_from_left_z(l[r]), lR = lane_from_right_z(l[r]);
+            const double mL = lane_from_left_z(m[r]), mR = lane_from_right_z(m[r]);
+            const double AL = lL + 2.0 * mL, AC = l[r] + 2.0 * m[r], AR = lR + 2.0 * mR;
+            const double AS = l[r - 1] + 2.0 * m[r - 1], AN = l[r + 1] + 2.0 * m[r + 1];
+            const double fy = top || bot ? 2.0 : 1.0, fx = xlo || xhi ? 2.0 : 1.0;
+            const double ax = fx * a[k] * A.cxx2, ay = fy * a[k] * A.cyy2, c = fx * fy * a[k] * A.cxy;
+            const double yN = top ? 0.0 : ay, yS = bot ? 0.0 : ay, xR = xhi ? 0.0 : ax, xL = xlo ? 0.0 : ax;
+            qu[k].xL = xL * (AC + AL);
+            qu[k].xR = xR * (AR + AC);
+            qu[k].yS = yS * (m[r] + m[r - 1]);
+            qu[k].yN = yN * (m[r + 1] + m[r]);
+            qu[k].cL = c * (xlo ? -l[r] : lL);
+            qu[k].cR = c * (xhi ? -l[r] : lR);
+            qu[k].cS = c * (bot ? -m[r] : m[r - 1]);
+            qu[k].cN = c * (top ? -m[r] : m[r + 1]);
+            qv[k].xL = xL * (m[r] + mL);
+            qv[k].xR = xR * (mR + m[r]);
+            qv[k].yS = yS * (AC + AS);
+            qv[k].yN = yN * (AN + AC);
+            qv[k].cL = c * (xlo ? -m[r] : mL);
+            qv[k].cR = c * (xhi ? -m[r] : mR);
+            qv[k].cS = c * (bot ? -l[r] : l[r - 1]);
+            qv[k].cN = c * (top ? -l[r] : l[r + 1]);
+        }
+    }
+    // the array rows (1 .. R) of the free faces in this wavefront, 0 if none
+    const int rtop = A.free_hi && A.ny >= row0 && A.ny < row0 + R ? A.ny - row0 + 1 : 0;
+    const int rbot = A.free_lo && 0 >= row0 && 0 < row0 + R ? 1 - row0 : 0;
+    auto ghosts = [&](double(&U)[R + 2], double(&V)[R + 2]) __attribute__((always_inline)) {
+        if (rtop | rbot) {
+#pragma unroll
+            for (int r = 1; r <= R; ++r) {
+                // (the empty asm keeps these rare, uniform branches from becoming selects)
+                if (rtop == r) {
+                    asm volatile("");
+                    U[r + 1] = U[r];
+                    V[r + 1] = V[r];
+                }
+                if (rbot == r) {
+                    asm volatile("");
+                    U[r - 1] = U[r];
+                    V[r - 1] = V[r];
+                }
+            }
+        }
+    };
+    ghosts(u0, v0);
+    const bool xface = TWO && __any(xlo || xhi);
+    auto left = [&](double x) __attribute__((always_inline)) {
+        double l = lane_from_left_z(x);
+        if (TWO && xface) {
+            asm volatile("");
+            l = xlo ? x : l;
+        }
+        return l;
+    };
+    auto right = [&](double x) __attribute__((always_inline)) {
+        double r = lane_from_right_z(x);
+        if (TWO && xface) {
+            asm volatile("");
+            r = xhi ? x : r;
+        }
+        return r;
+    };
+
+    // one step: X, Y the current level with its neighbour rows, U, V the level
+    // before, overwritten by the next one (the start: the second field, or unused)
+    auto step = [&](const double(&X)[R + 2], const double(&Y)[R + 2], double(&U)[R + 2], double(&V)[R + 2], int s,
+                    auto start, bool more) __attribute__((always_inline)) {
+        constexpr bool START = decltype(start)::value;
+        const double wk = A.wk[s], fc = A.fck[s];
+        double xSL = left(X[0]), xSR = right(X[0]), ySL = left(Y[0]), ySR = right(Y[0]);
+        double xL = left(X[1]), xR = right(X[1]), yL = left(Y[1]), yR = right(Y[1]);
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int r = k + 1;
+            const double xNL = left(X[r + 1]), xNR = right(X[r + 1]), yNL = left(Y[r + 1]), yNR = right(Y[r + 1]);
+            double su = stencil_row(qu[k], X[r], xL, xR, X[r - 1], X[r + 1], ySL, ySR, yNL, yNR);
+            double sv = stencil_row(qv[k], Y[r], yL, yR, Y[r - 1], Y[r + 1], xSL, xSR, xNL, xNR);
+            if constexpr (FORCE) {
+                su = fma(-fc, fu[k], su);
+                sv = fma(-fc, fv[k], sv);
+            }
+            double nu, nv;
+            if constexpr (START) {
+                nu = fma(0.5, su, X[r]);
+                nv = fma(0.5, sv, Y[r]);
+                au[k] = fma(A.w0, X[r], au[k]);
+                av[k] = fma(A.w0, Y[r], av[k]);
+                if constexpr (TWO) {
+                    const double(&g)[4][64] = dg[w * R + k];
+                    nu = fma(D.dtw * (1.0 - g[0][lane]), U[r], nu);
+                    nv = fma(D.dtw * (1.0 - g[2][lane]), V[r], nv);
+                    bu[k] = fma(D.w0v, U[r], bu[k]);
+                    bv[k] = fma(D.w0v, V[r], bv[k]);
+                }
+            } else {
+                nu = fma(2.0, X[r], -U[r]) + su;
+                nv = fma(2.0, Y[r], -V[r]) + sv;
+                if constexpr (TWO) {
+                    if (damped) {
+                        asm volatile("");
+                        const double(&g)[4][64] = dg[w * R + k];
+                        nu = fma(g[0][lane], U[r], nu) * g[1][lane];
+                        nv = fma(g[2][lane], V[r], nv) * g[3][lane];
+                    }
+                    bu[k] = fma(D.wvk[s], nu - U[r], bu[k]);
+                    bv[k] = fma(D.wvk[s], nv - V[r], bv[k]);
+                }
+            }
+            U[r] = nu;
+            V[r] = nv;
+            au[k] = fma(wk, nu, au[k]);
+            av[k] = fma(wk, nv, av[k]);
+            xSL = xL; xSR = xR; ySL = yL; ySR = yR;
+            xL = xNL; xR = xNR; yL = yNL; yR = yNR;
+        }
+        if (more) {
+            double(&e)[NW][2][2][64] = ex[s & 1];
+            e[w][0][0][lane] = U[1];
+            e[w][0][1][lane] = V[1];
+            e[w][1][0][lane] = U[R];
+            e[w][1][1][lane] = V[R];
+            __syncthreads();
+            const int wb = w > 0 ? w - 1 : w, wa = w < NW - 1 ? w + 1 : w;   // (the tile's outermost rows are not exact)
+            U[0] = e[wb][1][0][lane];
+            V[0] = e[wb][1][1][lane];
+            U[R + 1] = e[wa][0][0][lane];
+            V[R + 1] = e[wa][0][1][lane];
+            ghosts(U, V);
+        }
+    };
+    const std::false_type go{};
+    int s = 0;
+    if (A.first) {
+        // the start, then the levels exchange their arrays
+        step(u0, v0, u1, v1, 0, std::true_type{}, true);
+#pragma unroll
+        for (int r = 0; r < R + 2; ++r) {
+            double t = u0[r];
+            u0[r] = u1[r];
+            u1[r] = t;
+            t = v0[r];
+            v0[r] = v1[r];
+            v1[r] = t;
+        }
+        s = 1;
+    }
+    for (; s + 2 <= A.steps; s += 2) {
+        step(u0, v0, u1, v1, s, go, true);
+        step(u1, v1, u0, v0, s + 1, go, true);
+    }
+    // X, Y the level before the last, U, V the last
+    auto store = [&](const double(&X)[R + 2], const double(&Y)[R + 2], const double(&U)[R + 2],
+                     const double(&V)[R + 2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int j = row0 + k, q = w * R + k;
+            if (colu && j >= A.jlo && j <= A.jhi && lane >= A.H && lane < 64 - A.H && q >= A.H && q < NW * R - A.H) {
+                const int64_t o = (int64_t)j * P + col;
+                if (A.steps > 1) {
+                    outA[o] = X[k + 1];
+                    outA[o + CS] = Y[k + 1];
+                }
+                outB[o] = U[k + 1];
+                outB[o + CS] = V[k + 1];
+                acc[o] = au[k];
+                acc[o + CS] = av[k];
+                if constexpr (TWO) {
+                    D.acc1[o] = bu[k];
+                    D.acc1[o + CS] = bv[k];
+                }
+            }
+        }
+    };
+    if (s < A.steps) {   // one step more: the roles are exchanged
+        step(u0, v0, u1, v1, s, go, false);
+        store(u0, v0, u1, v1);
+    } else {
+        store(u1, v1, u0, v0);
+    }
+}
+
+template <int NW, int R, bool TWO>
+void tile_launch(bool force, hipStream_t s, const double* u, const double* uprev, double* outA, double* outB,
+                 const double* base, double* acc, const double* ca, const double* cl, const double* cm, const double* f,
+                 const Tile2D& A, const TwoField2D& D) {
+    const int cols = A.nx - 1 + (TWO ? D.xfree_lo + D.xfree_hi : 0), W = 64 - 2 * A.H, HV = NW * R - 2 * A.H;
+    const dim3 grid((unsigned)xcd_grid(((cols + W - 1) / W) * ((A.jhi - A.jlo + HV) / HV)));
+    if (force)
+        hipLaunchKernelGGL((tile2d_kernel<NW, R, true, TWO>), grid, dim3(64 * NW), 0, s, u, uprev, outA, outB, base,
+                           acc, ca, cl, cm, f, A, D);
+    else
+        hipLaunchKernelGGL((tile2d_kernel<NW, R, false, TWO>), grid, dim3(64 * NW), 0, s, u, uprev, outA, outB, base,
+                           acc, ca, cl, cm, f, A, D);
+}
+
+}  // namespace
+
+// The shape and steps per launch with the least modelled time of an application
+// of N steps.  Workgroups run in rounds, one per CU (their registers fill it):
+// a launch takes 1.5 us and each round the time of H steps (0.11 + 0.018 rows
+// us each: arithmetic of the tile's rows on four SIMDs, then the exchange) plus
+// 3 us of load latency and coefficients, 0.04 us per tile row for the loads
+// and 2.4 ns per inner node for its stores (two fields: 5 us and 6 ns).  Fitted
+// to, and within 15 % of, launches of 64^2 to 1500^2 nodes.  Measured, against
+// the marching kernels: 64^2 8 x 3 rows x 11 steps 1.18 us per step (3.91), 256^2
+// 8 x 4 x 12 1.47 (4.16), 611 x 373 8 x 4 x 6 2.20 (5.50), 1024^2 8 x 4 x 7 8.71
+// (10.75); two fields: 256^2 8 x 3 x 7 2.49 (7.01), 1024^2 8 x 3 x 6 14.2 (26.4),
+// where the 8 x 4 tile spills registers (20.8; with the velocity sum in LDS
+// instead 14.3 at 1024^2 and slower below).
+TileShape tile2d_pick(int nx, int nrows, int N, bool two) {
+    static const int shapes[3][2] = {{4, 4}, {8, 3}, {8, 4}};
+    const double fixed = two ? 5.0 : 3.0, store = two ? 6e-3 : 2.4e-3;
+    TileShape best;
+    double tbest = 1e300;
+    for (int k = 0; k < (two ? 2 : 3); ++k) {
+        const int rows = shapes[k][0] * shapes[k][1];
+        for (int H = 3; H <= std::min(kTileMaxSteps, rows / 2 - 1); ++H) {
+            const int W = 64 - 2 * H, HV = rows - 2 * H;
+            const long long tiles = (long long)((nx - 1 + W - 1) / W) * ((nrows + HV - 1) / HV);
+            const double rounds = (double)((tiles + 255) / 256);
+            const double t = (N + H - 1) / H * (1.5 + rounds * (fixed + 0.04 * rows + store * W * HV)) +
+                             rounds * N * (0.11 + 0.018 * rows);
+            if (t < tbest) {
+                tbest = t;
+                best.NW = shapes[k][0];
+                best.R = shapes[k][1];
+                best.H = H;
+            }
+        }
+    }
+    return best;
+}
+
+TileShape tile2d_shape(const elwh_ctx* c, bool two) {
+    // (fewer steps per launch, or a tiling, asked for: the marching kernels)
+    if (c->tile64_set || c->opts.fuse < 4) return TileShape();
+#ifdef TILE_PROBE
+    TileShape t;
+    if (const char* e = getenv("TILE")) {
+        sscanf(e, "%d,%d,%d", &t.NW, &t.R, &t.H);
+        return t;
+    }
+#endif
+    const int rows = c->mr.hi - c->mr.lo + 1;
+    // One field: beyond about 2000^2 nodes the marching kernels are level (2048^2:
+    // 2261 against 2364 us, 4096^2: 8.40 against 8.39 ms) and need no tile
+    // redundancy.  Two fields: they take one step per launch, 2.2 times slower.
+    if (!two && (int64_t)c->L.nx * rows > (int64_t)2100 * 2100) return TileShape();
+    return tile2d_pick(c->L.nx, rows, c->plan.nt * c->opts.periods + (two ? 1 : 0), two);
+}
+
+namespace {
+
+Tile2D tile_args(const elwh_ctx* c, const TileShape& t) {
+    Tile2D A{};
+    A.nx = c->L.nx;
+    A.ny = c->L.ny;
+    A.P = c->L.P;
+    A.CS = c->L.CS;
+    A.jlo = c->mr.lo;
+    A.jhi = c->mr.hi;
+    A.free_lo = c->mr.free_lo;
+    A.free_hi = c->mr.free_hi;
+    A.cxx2 = c->st.cxx2;
+    A.cyy2 = c->st.cyy2;
+    A.cxy = c->st.cxy;
+    A.H = t.H;
+    return A;
+}
+
+// The two state buffers that are neither a nor b.
+void other_two(const elwh_ctx* c, const double* a, const double* b, double** o) {
+    int k = 0;
+    for (double* p : c->s64)
+        if (k < 2 && p != a && p != b) o[k++] = p;
+}
+
+}  // namespace
+
+void run_filter_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool with_force, bool amode, double* out) {
+    const int nsteps = c->plan.nt * c->opts.periods;
+    const double sgn = amode ? -1.0 : 1.0;
+    Tile2D A = tile_args(c, t);
+    A.w0 = sgn * c->w[0];
+    const double *cur = x, *prev = nullptr;
+    prof_mark(c, 0);
+    prof_mark(c, 1);
+    for (int n = 0; n < nsteps; n += A.steps) {
+        A.first = n == 0;
+        A.steps = std::min(t.H, nsteps - n);
+        for (int s = 0; s < A.steps; ++s) {
+            A.wk[s] = sgn * c->w[n + s + 1];
+            A.fck[s] = c->cosn[n + s];
+        }
+        double* o[2] = {nullptr, nullptr};
+        other_two(c, cur, prev, o);
+        const auto launch = t.NW == 4 ? tile_launch<4, 4, false>
+                                      : (t.R == 3 ? tile_launch<8, 3, false> : tile_launch<8, 4, false>);
+        launch(with_force, c->stream, cur, prev, o[0], o[1], amode ? x : nullptr, out, c->ca, c->cl, c->cm, c->f64, A,
+               TwoField2D{});
+        prev = A.steps > 1 ? o[0] : cur;
+        cur = o[1];
+    }
+    prof_mark(c, 2, nsteps - 1);
+}
+
+void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x0, const double* z1, bool with_force,
+                                bool amode, double s_in, double s_out, double* out0, double* out1) {
+    const int N = c->plan.nt * c->opts.periods;   // and one step more, for the velocity of the last level
+    const double sgn = amode ? -1.0 : 1.0, dt = c->plan.dt;
+    Tile2D A = tile_args(c, t);
+    A.w0 = sgn * c->w[0];
+    TwoField2D D{};
+    D.base1 = amode ? z1 : nullptr;
+    D.acc1 = out1;
+    D.dmp = c->dmp;
+    D.dmpx = c->dmpx;
+    D.imp_lo = c->imp[0];
+    D.imp_hi = c->imp[1];
+    D.xfree_lo = c->ximp[0];
+    D.xfree_hi = c->ximp[1];
+    D.w0v = sgn * c->w[0] * s_in * s_out;
+    D.dtw = dt * s_in;
+    const double *cur = x0, *prev = z1;
+    prof_mark(c, 0);
+    prof_mark(c, 1);
+    for (int n = 0; n <= N; n += A.steps) {
+        A.first = n == 0;
+        A.steps = std::min(t.H, N + 1 - n);
+        for (int s = 0; s < A.steps; ++s) {
+            A.wk[s] = n + s < N ? sgn * c->w[n + s + 1] : 0.0;
+            A.fck[s] = c->cosn[n + s];
+            D.wvk[s] = sgn * c->w[n + s] * s_out / (2.0 * dt);
+        }
+        double* o[2] = {nullptr, nullptr};
+        other_two(c, cur, prev, o);
+        const auto launch = t.NW == 4 ? tile_launch<4, 4, true> : tile_launch<8, 3, true>;
+        launch(with_force, c->stream, cur, prev, o[0], o[1], amode ? x0 : nullptr, out0, c->ca, c->cl, c->cm, c->f64, A,
+               D);
+        prev = A.steps > 1 ? o[0] : cur;
+        cur = o[1];
+    }
+    prof_mark(c, 2, N);
+}
+
+}  // namespace elwh
