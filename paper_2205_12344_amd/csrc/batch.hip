@@ -44,6 +44,8 @@ struct elwh_batch {
     Tile tile[2];                   // [0] FP64, [1] FP32
     std::vector<BProb2D> h_pr;
     std::vector<int> full_blk, full_blk2;   // tiles of each problem in the two tilings of the phase
+    bool reg = false;               // FP64 phases take register-tile ticks
+    int H = 0;                      // their steps per tick in the current phase (0: marching ticks)
     BProb2D* d_pr = nullptr;
     std::vector<BState> h_st;
     BState* d_st = nullptr;
@@ -59,7 +61,7 @@ struct elwh_batch {
     double* h_dots = nullptr;       // pinned
     std::vector<double*> d_w, d_cos;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
-    int gblocks[2] = {0, 0}, gblocks2[2] = {0, 0};
+    int gblocks[2] = {0, 0}, gblocks2[2] = {0, 0}, gH = 0;
     std::vector<elwh_info> info;
     double seconds = 0;
     long long ticks = 0;
@@ -83,6 +85,17 @@ thread_local std::string g_batch_err;
         if (s_ != ELWH_OK) return s_; \
     } while (0)
 
+// Steps per register-tile tick for the problems of live (null: all).
+int reg_steps(const elwh_batch* b, const std::vector<BState>* live) {
+    std::vector<BatchSize> v;
+    for (int p = 0; p < b->np; ++p) {
+        const elwh_ctx* c = b->ctx[p];
+        if (!live || (*live)[p].active)
+            v.push_back(BatchSize{c->L.nx, c->mr.hi - c->mr.lo + 1, c->plan.nt * c->opts.periods});
+    }
+    return batch_reg_steps(v);
+}
+
 // Descriptors of every problem for one phase (precision fp32), vector roles
 // given by indices into the context's work vectors.
 elwh_status set_phase(elwh_batch* b, bool fp32, int isrc, int iout, int ix, int ir, int ip, int* nblocks,
@@ -91,6 +104,7 @@ elwh_status set_phase(elwh_batch* b, bool fp32, int isrc, int iout, int ix, int 
     const int W = batch_cols(t.V), W2 = batch_cols_k(t.V, batch_kb(b->opts.fuse));
     int off = 0, off2 = 0;
     b->h_pr.resize(b->np);
+    b->H = b->reg && !fp32 ? reg_steps(b, nullptr) : 0;
     for (int p = 0; p < b->np; ++p) {
         elwh_ctx* c = b->ctx[p];
         BProb2D& q = b->h_pr[p];
@@ -103,8 +117,9 @@ elwh_status set_phase(elwh_batch* b, bool fp32, int isrc, int iout, int ix, int 
         off += q.nblk;
         q.nbx2 = (q.A.nx - 1 + W2) / W2;
         q.nblk2 = q.nbx2 * ((nrows + t.TY - 1) / t.TY);
+        if (b->H > 0) q.nblk2 = batch_reg_tiles(q.A.nx, nrows, b->H, &q.nbx2);
         q.off2 = off2;
-        off2 += q.nblk2;
+        off2 += b->H > 0 ? (q.nblk2 + 7) / 8 : q.nblk2;   // (register tiles are dealt per XCD)
         q.nsteps = c->plan.nt * c->opts.periods;
         q.w = b->d_w[p];
         q.cosn = b->d_cos[p];
@@ -160,15 +175,17 @@ elwh_status list_active(elwh_batch* b) {
 // problems; the launch sizes shrink with the active set.
 elwh_status retile_active(elwh_batch* b, int* nblocks, int* nblocks2) {
     int off = 0, off2 = 0;
+    if (b->H > 0) b->H = reg_steps(b, &b->h_st);   // (any tick may change it)
     for (int p = 0; p < b->np; ++p) {
         BProb2D& q = b->h_pr[p];
         const bool live = b->h_st[p].active != 0;
+        if (b->H > 0) b->full_blk2[p] = batch_reg_tiles(q.A.nx, q.A.jhi - q.A.jlo + 1, b->H, &q.nbx2);
         q.off = off;
         q.nblk = live ? b->full_blk[p] : 0;
         off += q.nblk;
         q.off2 = off2;
         q.nblk2 = live ? b->full_blk2[p] : 0;
-        off2 += q.nblk2;
+        off2 += b->H > 0 ? (q.nblk2 + 7) / 8 : q.nblk2;
     }
     *nblocks = off;
     *nblocks2 = off2;
@@ -195,9 +212,10 @@ elwh_status upload_mask(elwh_batch* b, const std::vector<int>& mask) {
     return ELWH_OK;
 }
 
-// Ticks of one application: the half step, then kb-step ticks while kb or
-// more steps are left, single steps otherwise.
-int ticks_per_application(int nsteps, int kb) {
+// Ticks of one application: register tiles, H steps each; else the half step,
+// then kb-step ticks while kb or more steps are left, single steps otherwise.
+int ticks_per_application(int nsteps, int kb, int H) {
+    if (H > 0) return (nsteps + H - 1) / H;
     const int rest = nsteps - 1;
     return 1 + (kb >= 2 ? rest / kb + rest % kb : rest);
 }
@@ -215,19 +233,23 @@ elwh_status run_apply(elwh_batch* b, bool fp32, bool force, bool amode, int isrc
         s.n = 0;
         s.end = 0;
         s.active = sel[p] ? 1 : 0;
-        if (sel[p]) maxticks = std::max(maxticks, ticks_per_application(b->h_pr[p].nsteps, kb));
+        if (sel[p]) maxticks = std::max(maxticks, ticks_per_application(b->h_pr[p].nsteps, kb, b->H));
     }
     BST(upload_states(b));
     const Tile& t = b->tile[fp32 ? 1 : 0];
     const bool comp = fp32 && b->opts.compensated;
     const double sgn = amode ? -1.0 : 1.0;
     for (int k = 0; k < maxticks; ++k) {
-        launch_batch_step(fp32, t.V, t.TY, force, comp, nblocks, b->stream, b->d_pr, b->d_st, b->np, sgn,
-                          amode ? 1 : 0, kb);
-        if (kb)
-            launch_batch_multi(fp32, t.V, t.TY, kb, force, comp, nblocks2, b->stream, b->d_pr, b->d_st, b->np, sgn,
-                               amode ? 1 : 0);
-        launch_batch_advance(b->stream, b->d_pr, b->d_st, b->np, 1, kb, fp32 ? 1 : 0);
+        if (b->H > 0) {
+            launch_batch_tiles(force, nblocks2, b->H, b->stream, b->d_pr, b->d_st, b->np, sgn, amode ? 1 : 0);
+        } else {
+            launch_batch_step(fp32, t.V, t.TY, force, comp, nblocks, b->stream, b->d_pr, b->d_st, b->np, sgn,
+                              amode ? 1 : 0, kb);
+            if (kb)
+                launch_batch_multi(fp32, t.V, t.TY, kb, force, comp, nblocks2, b->stream, b->d_pr, b->d_st, b->np,
+                                   sgn, amode ? 1 : 0);
+        }
+        launch_batch_advance(b->stream, b->d_pr, b->d_st, b->np, 1, kb, fp32 ? 1 : 0, b->H);
         b->ticks++;
     }
     BCK(hipGetLastError());
@@ -319,11 +341,15 @@ void enqueue_ticks(elwh_batch* b, bool fp32, int nblocks, int nblocks2, int ntic
     const bool comp = fp32 && b->opts.compensated;
     const int kb = batch_kb(b->opts.fuse);
     for (int k = 0; k < nticks; ++k) {
-        launch_batch_step(fp32, t.V, t.TY, false, comp, nblocks, b->stream, b->d_pr, b->d_st, b->np, -1.0, 1, kb);
-        if (kb)
-            launch_batch_multi(fp32, t.V, t.TY, kb, false, comp, nblocks2, b->stream, b->d_pr, b->d_st, b->np, -1.0,
-                               1);
-        launch_batch_advance(b->stream, b->d_pr, b->d_st, b->np, 0, kb, fp32 ? 1 : 0);
+        if (b->H > 0) {
+            launch_batch_tiles(false, nblocks2, b->H, b->stream, b->d_pr, b->d_st, b->np, -1.0, 1);
+        } else {
+            launch_batch_step(fp32, t.V, t.TY, false, comp, nblocks, b->stream, b->d_pr, b->d_st, b->np, -1.0, 1, kb);
+            if (kb)
+                launch_batch_multi(fp32, t.V, t.TY, kb, false, comp, nblocks2, b->stream, b->d_pr, b->d_st, b->np,
+                                   -1.0, 1);
+        }
+        launch_batch_advance(b->stream, b->d_pr, b->d_st, b->np, 0, kb, fp32 ? 1 : 0, b->H);
         for (int mode = 0; mode < 3; ++mode)
             launch_batch_cg(b->stream, mode, b->d_pr, b->d_st, b->np, b->d_plist, b->nplist, b->d_partials,
                             b->d_arrive, b->d_active);
@@ -332,7 +358,8 @@ void enqueue_ticks(elwh_batch* b, bool fp32, int nblocks, int nblocks2, int ntic
 
 elwh_status graph_for(elwh_batch* b, bool fp32, int nblocks, int nblocks2) {
     const int k = fp32 ? 1 : 0;
-    if (b->gexec[k] && b->gblocks[k] == nblocks && b->gblocks2[k] == nblocks2 && b->gnplist[k] == b->nplist)
+    if (b->gexec[k] && b->gblocks[k] == nblocks && b->gblocks2[k] == nblocks2 && b->gnplist[k] == b->nplist &&
+        (fp32 || b->gH == b->H))
         return ELWH_OK;
     if (b->gexec[k]) {
         (void)hipGraphExecDestroy(b->gexec[k]);
@@ -352,6 +379,7 @@ elwh_status graph_for(elwh_batch* b, bool fp32, int nblocks, int nblocks2) {
     b->gblocks[k] = nblocks;
     b->gblocks2[k] = nblocks2;
     b->gnplist[k] = b->nplist;
+    if (!fp32) b->gH = b->H;
     return ELWH_OK;
 }
 
@@ -541,8 +569,10 @@ elwh_status elwh_batch_create(int nprob, const elwh_grid* grids, const double* c
     const Tile t0 = batch_kb(o.fuse) == 4 ? Tile{1, 10} : Tile{2, 8};
     b->tile[0] = t0;
     b->tile[1] = t0;
+    b->reg = batch_kb(o.fuse) == 4;   // (fewer steps per tick asked for: the marching kernels)
     if (o.autotune) {
-        if (autotune_batch(b, false) != ELWH_OK) return fail(ELWH_ERR_HIP, b->err);
+        // (register-tile ticks choose their steps from the sizes)
+        if (!b->reg && autotune_batch(b, false) != ELWH_OK) return fail(ELWH_ERR_HIP, b->err);
         if (o.prec == ELWH_FP32_STEP && autotune_batch(b, true) != ELWH_OK) return fail(ELWH_ERR_HIP, b->err);
     }
     if (hipStreamSynchronize(b->stream) != hipSuccess) return fail(ELWH_ERR_HIP, "synchronisation failed");

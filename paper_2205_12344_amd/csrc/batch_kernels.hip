@@ -13,13 +13,21 @@ namespace elwh {
 // application per problem (deactivate when it completes).  After the half
 // step u^{n-1} = u^0 is src in FP64 and s[0] in FP32.
 __global__ void batch_advance_kernel(const BProb2D* __restrict__ pr, BState* __restrict__ st, int np, int single,
-                                     int kb, int fp32) {
+                                     int kb, int fp32, int H) {
     const int p = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (p >= np || !st[p].active) return;
     BState& s = st[p];
     const int neff = s.end ? 0 : s.n;
     int steps = 1;
-    if (neff == 0) {
+    if (H > 0) {
+        // register tiles: the last two levels went to the two free buffers
+        const int ic = neff == 0 ? -1 : s.ic, ip = neff == 0 ? -1 : s.ip;
+        int x1, x2;
+        batch_free_two(ic, ip, x1, x2);
+        steps = min(H, pr[p].nsteps - neff);
+        s.ip = steps > 1 ? x1 : ic;
+        s.ic = x2;
+    } else if (neff == 0) {
         s.ip = fp32 ? 0 : -1;
         s.ic = 1;
     } else if (batch_multi_step(neff, pr[p].nsteps, kb)) {
@@ -213,8 +221,8 @@ __global__ __launch_bounds__(64) void batch_dot_final_kernel(int np, const int* 
     if (threadIdx.x == 0) out[p] = s;
 }
 
-void launch_batch_advance(hipStream_t s, const BProb2D* pr, BState* st, int np, int single, int kb, int fp32) {
-    hipLaunchKernelGGL(batch_advance_kernel, dim3((np + 63) / 64), dim3(64), 0, s, pr, st, np, single, kb, fp32);
+void launch_batch_advance(hipStream_t s, const BProb2D* pr, BState* st, int np, int single, int kb, int fp32, int H) {
+    hipLaunchKernelGGL(batch_advance_kernel, dim3((np + 63) / 64), dim3(64), 0, s, pr, st, np, single, kb, fp32, H);
 }
 
 void launch_batch_cg(hipStream_t s, int mode, const BProb2D* pr, BState* st, int np, const int* plist, int nplist,

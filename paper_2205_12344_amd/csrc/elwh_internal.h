@@ -367,12 +367,23 @@ enum { RED_SUM = 0, RED_PQ = 1, RED_RR = 2 };
 // for four steps per launch, 2 for two or three, 0 for single steps only.
 inline int batch_kb(int fuse) { return fuse >= 4 ? 4 : (fuse >= 2 ? 2 : 0); }
 bool batch_tile_valid(bool fp32, int V, int TY, int kb);
+// Register-tile ticks of an FP64 batch (kernels2d_tile.hip): tiles of a problem
+// (and tiles along x), the steps per tick for a set of problems, and the tick
+// (neighths: the sum over problems of an eighth of their tiles, rounded up).
+struct BatchSize {
+    int nx, nrows, nsteps;
+};
+int batch_reg_tiles(int nx, int nrows, int H, int* ntx);
+int batch_reg_steps(const std::vector<BatchSize>& probs);
+void launch_batch_tiles(bool force, int neighths, int H, hipStream_t s, const BProb2D* pr, const BState* st, int np,
+                        double sgn, int amode);
 int batch_cols(int V);
 Args2D make_args2d(const elwh_ctx* c);
 void launch_batch_step(bool fp32, int V, int TY, bool force, bool comp, int nblocks, hipStream_t s,
                        const BProb2D* pr, const BState* st, int np, double sgn, int amode, int kb);
-// problems with kb or more steps left (kb = 2, 4) take a kb-step launch
-void launch_batch_advance(hipStream_t s, const BProb2D* pr, BState* st, int np, int single, int kb, int fp32);
+// problems with kb or more steps left (kb = 2, 4) take a kb-step launch; H > 0:
+// register-tile ticks of up to H steps
+void launch_batch_advance(hipStream_t s, const BProb2D* pr, BState* st, int np, int single, int kb, int fp32, int H);
 // computed columns per wavefront of the kb-step tiling (kb = 2 or 4)
 int batch_cols_k(int V, int kb);
 // kb-step tick of every active problem with at least kb steps left in its

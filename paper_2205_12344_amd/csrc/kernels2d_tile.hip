@@ -31,7 +31,6 @@
 // The launch that starts an application takes the even-in-time start u^1 = u^0
 // + (a/2)(Ltilde u^0 - f) (with a second field, + dt (1 - g) u1) as its first step.
 #include <algorithm>
-#include <type_traits>
 #include <cstdio>
 #include <cstdlib>
 
@@ -60,29 +59,44 @@ __device__ __forceinline__ double stencil_row(const Coef& q, double C, double L,
     return fma(-q.cS, oSR - oSL, s);
 }
 
-template <int NW, int R, bool FORCE, bool TWO>
-__global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restrict__ u, const double* __restrict__ uprev,
-                                                         double* __restrict__ outA, double* __restrict__ outB,
-                                                         const double* __restrict__ base, double* __restrict__ acc,
-                                                         const double* __restrict__ ca, const double* __restrict__ cl,
-                                                         const double* __restrict__ cm, const double* __restrict__ f,
-                                                         Tile2D A, TwoField2D D) {
+// Weights of a launch's steps: w(s) of the level step s computes, f(s) the
+// forcing factor of the level it starts from.
+struct ArgWeights {
+    const Tile2D& A;
+    __device__ double w(int s) const { return A.wk[s]; }
+    __device__ double f(int s) const { return A.fck[s]; }
+};
+struct TableWeights {
+    const double *wt, *ct;
+    double sgn;
+    __device__ double w(int s) const { return sgn * wt[s]; }
+    __device__ double f(int s) const { return ct[s]; }
+};
+
+// Tile (tx, ty) of one problem.
+template <int NW, int R, bool FORCE, bool TWO, class Weights>
+__device__ __forceinline__ void tile2d_body(int tx, int ty, const double* __restrict__ u,
+                                            const double* __restrict__ uprev, double* __restrict__ outA,
+                                            double* __restrict__ outB, const double* __restrict__ base,
+                                            double* __restrict__ acc, const double* __restrict__ ca,
+                                            const double* __restrict__ cl, const double* __restrict__ cm,
+                                            const double* __restrict__ f, const Tile2D& A, const TwoField2D& D,
+                                            const Weights& W) {
     __shared__ double ex[2][NW][2][2][64];   // [buffer][wavefront][first, last row][u, v][column]
+    // a f per node (each lane its own values: registers are full)
+    __shared__ double af[FORCE ? NW * R : 1][2][64];
     // damping of the tile's face nodes: g, 1 / (1 + g) of u, then of v
     __shared__ double dg[TWO ? NW * R : 1][4][64];
+    __shared__ double zs[TWO ? NW * R : 1][2][64];   // the second field (first launch)
     const int ilo = TWO && D.xfree_lo ? 0 : 1, ihi = TWO && D.xfree_hi ? A.nx : A.nx - 1;   // unknown columns
-    const int ntx = (ihi - ilo + 64 - 2 * A.H) / (64 - 2 * A.H);
-    const int HV = NW * R - 2 * A.H, nty = (A.jhi - A.jlo + HV) / HV;
-    int t;
-    if (!xcd_tile((int)blockIdx.x, ntx * nty, t)) return;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: scalar row indices)
-    const int col = ilo + (t % ntx) * (64 - 2 * A.H) - A.H + lane;
-    const int row0 = A.jlo + (t / ntx) * HV - A.H + w * R;   // first row of this wavefront
+    const int col = ilo + tx * (64 - 2 * A.H) - A.H + lane;
+    const int row0 = A.jlo + ty * (NW * R - 2 * A.H) - A.H + w * R;   // first row of this wavefront
     const bool colv = col >= 0 && col <= A.nx, colu = col >= ilo && col <= ihi;
     const int64_t P = A.P, CS = A.CS;
 
     // rows 0 and R + 1 of these arrays are the neighbours' (row r = grid row row0 + r - 1)
-    double u0[R + 2], v0[R + 2], u1[R + 2], v1[R + 2], au[R], av[R], fu[R], fv[R], bu[R], bv[R];
+    double u0[R + 2], v0[R + 2], u1[R + 2], v1[R + 2], au[R], av[R], bu[R], bv[R];
     const bool xlo = TWO && D.xfree_lo && col == 0, xhi = TWO && D.xfree_hi && col == A.nx;
     bool damped = false;   // (uniform) this wavefront has nodes of an impedance face
     Coef qu[R], qv[R];
@@ -100,8 +114,9 @@ __global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restric
             if (r >= 1 && r <= R) {
                 const bool unk = colu && j >= A.jlo && j <= A.jhi;
                 a[r - 1] = unk ? ca[o] : 0.0;
-                u1[r] = unk && uprev ? uprev[o] : 0.0;
-                v1[r] = unk && uprev ? uprev[o + CS] : 0.0;
+                const bool older = unk && uprev && !(TWO && A.first);
+                u1[r] = older ? uprev[o] : 0.0;
+                v1[r] = older ? uprev[o + CS] : 0.0;
                 const int q = w * R + r - 1;
                 const bool own = unk && lane >= A.H && lane < 64 - A.H && q >= A.H && q < NW * R - A.H;
                 const double* b = A.first ? base : acc;
@@ -122,14 +137,20 @@ __global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restric
                         gu += g[0];
                         gv += g[A.ny + 1];
                     }
+                    if (A.first) {
+                        zs[q][0][lane] = unk ? uprev[o] : 0.0;
+                        zs[q][1][lane] = unk ? uprev[o + CS] : 0.0;
+                    }
                     dg[q][0][lane] = gu;
                     dg[q][1][lane] = 1.0 / (1.0 + gu);
                     dg[q][2][lane] = gv;
                     dg[q][3][lane] = 1.0 / (1.0 + gv);
                     damped |= __any(gu != 0.0 || gv != 0.0);
                 }
-                fu[r - 1] = FORCE && unk ? ca[o] * f[o] : 0.0;
-                fv[r - 1] = FORCE && unk ? ca[o] * f[o + CS] : 0.0;
+                if constexpr (FORCE) {
+                    af[q][0][lane] = unk ? ca[o] * f[o] : 0.0;
+                    af[q][1][lane] = unk ? ca[o] * f[o + CS] : 0.0;
+                }
             }
         }
         u1[0] = u1[R + 1] = v1[0] = v1[R + 1] = 0.0;
@@ -202,12 +223,20 @@ __global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restric
         return r;
     };
 
+    if (A.first) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            au[k] = fma(A.w0, u0[k + 1], au[k]);
+            av[k] = fma(A.w0, v0[k + 1], av[k]);
+        }
+    }
+
     // one step: X, Y the current level with its neighbour rows, U, V the level
-    // before, overwritten by the next one (the start: the second field, or unused)
+    // before, overwritten by the next one (before the start: 0)
     auto step = [&](const double(&X)[R + 2], const double(&Y)[R + 2], double(&U)[R + 2], double(&V)[R + 2], int s,
-                    auto start, bool more) __attribute__((always_inline)) {
-        constexpr bool START = decltype(start)::value;
-        const double wk = A.wk[s], fc = A.fck[s];
+                    bool more) __attribute__((always_inline)) {
+        const bool start = s == 0 && A.first;
+        const double wk = W.w(s), fc = FORCE ? W.f(s) : 0.0;
         double xSL = left(X[0]), xSR = right(X[0]), ySL = left(Y[0]), ySR = right(Y[0]);
         double xL = left(X[1]), xR = right(X[1]), yL = left(Y[1]), yR = right(Y[1]);
 #pragma unroll
@@ -217,35 +246,31 @@ __global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restric
             double su = stencil_row(qu[k], X[r], xL, xR, X[r - 1], X[r + 1], ySL, ySR, yNL, yNR);
             double sv = stencil_row(qv[k], Y[r], yL, yR, Y[r - 1], Y[r + 1], xSL, xSR, xNL, xNR);
             if constexpr (FORCE) {
-                su = fma(-fc, fu[k], su);
-                sv = fma(-fc, fv[k], sv);
+                su = fma(-fc, af[w * R + k][0][lane], su);
+                sv = fma(-fc, af[w * R + k][1][lane], sv);
             }
-            double nu, nv;
-            if constexpr (START) {
-                nu = fma(0.5, su, X[r]);
-                nv = fma(0.5, sv, Y[r]);
-                au[k] = fma(A.w0, X[r], au[k]);
-                av[k] = fma(A.w0, Y[r], av[k]);
+            double nu = fma(2.0, X[r], -U[r]) + su, nv = fma(2.0, Y[r], -V[r]) + sv;
+            if (start) {   // half of it, plus the second field
+                asm volatile("");
+                nu *= 0.5;
+                nv *= 0.5;
                 if constexpr (TWO) {
                     const double(&g)[4][64] = dg[w * R + k];
-                    nu = fma(D.dtw * (1.0 - g[0][lane]), U[r], nu);
-                    nv = fma(D.dtw * (1.0 - g[2][lane]), V[r], nv);
-                    bu[k] = fma(D.w0v, U[r], bu[k]);
-                    bv[k] = fma(D.w0v, V[r], bv[k]);
+                    const double zu = zs[w * R + k][0][lane], zv = zs[w * R + k][1][lane];
+                    nu = fma(D.dtw * (1.0 - g[0][lane]), zu, nu);
+                    nv = fma(D.dtw * (1.0 - g[2][lane]), zv, nv);
+                    bu[k] = fma(D.w0v, zu, bu[k]);
+                    bv[k] = fma(D.w0v, zv, bv[k]);
                 }
-            } else {
-                nu = fma(2.0, X[r], -U[r]) + su;
-                nv = fma(2.0, Y[r], -V[r]) + sv;
-                if constexpr (TWO) {
-                    if (damped) {
-                        asm volatile("");
-                        const double(&g)[4][64] = dg[w * R + k];
-                        nu = fma(g[0][lane], U[r], nu) * g[1][lane];
-                        nv = fma(g[2][lane], V[r], nv) * g[3][lane];
-                    }
-                    bu[k] = fma(D.wvk[s], nu - U[r], bu[k]);
-                    bv[k] = fma(D.wvk[s], nv - V[r], bv[k]);
+            } else if constexpr (TWO) {
+                if (damped) {
+                    asm volatile("");
+                    const double(&g)[4][64] = dg[w * R + k];
+                    nu = fma(g[0][lane], U[r], nu) * g[1][lane];
+                    nv = fma(g[2][lane], V[r], nv) * g[3][lane];
                 }
+                bu[k] = fma(D.wvk[s], nu - U[r], bu[k]);
+                bv[k] = fma(D.wvk[s], nv - V[r], bv[k]);
             }
             U[r] = nu;
             V[r] = nv;
@@ -269,25 +294,10 @@ __global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restric
             ghosts(U, V);
         }
     };
-    const std::false_type go{};
     int s = 0;
-    if (A.first) {
-        // the start, then the levels exchange their arrays
-        step(u0, v0, u1, v1, 0, std::true_type{}, true);
-#pragma unroll
-        for (int r = 0; r < R + 2; ++r) {
-            double t = u0[r];
-            u0[r] = u1[r];
-            u1[r] = t;
-            t = v0[r];
-            v0[r] = v1[r];
-            v1[r] = t;
-        }
-        s = 1;
-    }
     for (; s + 2 <= A.steps; s += 2) {
-        step(u0, v0, u1, v1, s, go, true);
-        step(u1, v1, u0, v0, s + 1, go, true);
+        step(u0, v0, u1, v1, s, true);
+        step(u1, v1, u0, v0, s + 1, true);
     }
     // X, Y the level before the last, U, V the last
     auto store = [&](const double(&X)[R + 2], const double(&Y)[R + 2], const double(&U)[R + 2],
@@ -313,19 +323,38 @@ __global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restric
         }
     };
     if (s < A.steps) {   // one step more: the roles are exchanged
-        step(u0, v0, u1, v1, s, go, false);
+        step(u0, v0, u1, v1, s, false);
         store(u0, v0, u1, v1);
     } else {
         store(u1, v1, u0, v0);
     }
 }
 
+__host__ __device__ __forceinline__ int tiles_x(int cols, int H) { return (cols + 63 - 2 * H) / (64 - 2 * H); }
+__host__ __device__ __forceinline__ int tiles_y(int nrows, int rows, int H) {
+    return (nrows + rows - 2 * H - 1) / (rows - 2 * H);
+}
+
+template <int NW, int R, bool FORCE, bool TWO>
+__global__ __launch_bounds__(64 * NW) void tile2d_kernel(const double* __restrict__ u, const double* __restrict__ uprev,
+                                                         double* __restrict__ outA, double* __restrict__ outB,
+                                                         const double* __restrict__ base, double* __restrict__ acc,
+                                                         const double* __restrict__ ca, const double* __restrict__ cl,
+                                                         const double* __restrict__ cm, const double* __restrict__ f,
+                                                         Tile2D A, TwoField2D D) {
+    const int ntx = tiles_x(A.nx - 1 + (TWO ? D.xfree_lo + D.xfree_hi : 0), A.H);
+    int t;
+    if (!xcd_tile((int)blockIdx.x, ntx * tiles_y(A.jhi - A.jlo + 1, NW * R, A.H), t)) return;
+    tile2d_body<NW, R, FORCE, TWO>(t % ntx, t / ntx, u, uprev, outA, outB, base, acc, ca, cl, cm, f, A, D,
+                                   ArgWeights{A});
+}
+
 template <int NW, int R, bool TWO>
 void tile_launch(bool force, hipStream_t s, const double* u, const double* uprev, double* outA, double* outB,
                  const double* base, double* acc, const double* ca, const double* cl, const double* cm, const double* f,
                  const Tile2D& A, const TwoField2D& D) {
-    const int cols = A.nx - 1 + (TWO ? D.xfree_lo + D.xfree_hi : 0), W = 64 - 2 * A.H, HV = NW * R - 2 * A.H;
-    const dim3 grid((unsigned)xcd_grid(((cols + W - 1) / W) * ((A.jhi - A.jlo + HV) / HV)));
+    const int cols = A.nx - 1 + (TWO ? D.xfree_lo + D.xfree_hi : 0);
+    const dim3 grid((unsigned)xcd_grid(tiles_x(cols, A.H) * tiles_y(A.jhi - A.jlo + 1, NW * R, A.H)));
     if (force)
         hipLaunchKernelGGL((tile2d_kernel<NW, R, true, TWO>), grid, dim3(64 * NW), 0, s, u, uprev, outA, outB, base,
                            acc, ca, cl, cm, f, A, D);
@@ -356,10 +385,9 @@ TileShape tile2d_pick(int nx, int nrows, int N, bool two) {
     for (int k = 0; k < (two ? 2 : 3); ++k) {
         const int rows = shapes[k][0] * shapes[k][1];
         for (int H = 3; H <= std::min(kTileMaxSteps, rows / 2 - 1); ++H) {
-            const int W = 64 - 2 * H, HV = rows - 2 * H;
-            const long long tiles = (long long)((nx - 1 + W - 1) / W) * ((nrows + HV - 1) / HV);
-            const double rounds = (double)((tiles + 255) / 256);
-            const double t = (N + H - 1) / H * (1.5 + rounds * (fixed + 0.04 * rows + store * W * HV)) +
+            const long long tiles = (long long)tiles_x(nx - 1, H) * tiles_y(nrows, rows, H);
+            const double rounds = (double)((tiles + 255) / 256), inner = (64 - 2 * H) * (rows - 2 * H);
+            const double t = (N + H - 1) / H * (1.5 + rounds * (fixed + 0.04 * rows + store * inner)) +
                              rounds * N * (0.11 + 0.018 * rows);
             if (t < tbest) {
                 tbest = t;
@@ -482,6 +510,102 @@ void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x
         cur = o[1];
     }
     prof_mark(c, 2, N);
+}
+
+// ===========================================================================
+// Ragged batch: one register-tile tick advances every active problem by up to H
+// steps of its own application (the start included), in one launch over the
+// concatenated tiles.
+// ===========================================================================
+namespace {
+
+constexpr int BNW = 8, BR = 4;
+
+template <bool FORCE>
+__global__ __launch_bounds__(64 * BNW) void batch_tile2d_kernel(const BProb2D* __restrict__ pr,
+                                                               const BState* __restrict__ st, int np, int H, double sgn,
+                                                               int amode) {
+    // XCD x takes one eighth of every problem's tiles (off2 counts eighths), so
+    // the XCDs stay even when some problems have finished: dealt in one band over
+    // all problems, the tiles of the problems left fell to one or two XCDs
+    // (batch of 16 problems of 256^2 to 1024^2: 237 ms for three iterations).
+    const int x = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
+    const int p = batch_problem_of(pr, np, slot, true);
+    const BProb2D& q = pr[p];
+    if (!st[p].active) return;
+    const int local = x * ((q.nblk2 + kXcds - 1) / kXcds) + slot - q.off2, n = st[p].end ? 0 : st[p].n;
+    if (slot - q.off2 >= (q.nblk2 + kXcds - 1) / kXcds || local >= q.nblk2) return;
+    Tile2D A;
+    A.nx = q.A.nx;
+    A.ny = q.A.ny;
+    A.P = q.A.P;
+    A.CS = q.A.CS;
+    A.jlo = q.A.jlo;
+    A.jhi = q.A.jhi;
+    A.free_lo = q.A.free_lo;
+    A.free_hi = q.A.free_hi;
+    A.cxx2 = q.A.cxx2;
+    A.cyy2 = q.A.cyy2;
+    A.cxy = q.A.cxy;
+    A.H = H;
+    A.first = n == 0;
+    A.steps = min(H, q.nsteps - n);
+    A.w0 = sgn * q.w[0];
+    const int ic = n == 0 ? -1 : st[p].ic, ip = n == 0 ? -1 : st[p].ip;
+    int x1, x2;
+    batch_free_two(ic, ip, x1, x2);
+    const double* cur = ic >= 0 ? static_cast<const double*>(q.s[ic]) : q.src;
+    const double* prev = n == 0 ? nullptr : (ip >= 0 ? static_cast<const double*>(q.s[ip]) : q.src);
+    const TableWeights W{q.w + n + 1, q.cosn + n, sgn};
+    tile2d_body<BNW, BR, FORCE, false>(local % q.nbx2, local / q.nbx2, cur, prev, static_cast<double*>(q.s[x1]),
+                                       static_cast<double*>(q.s[x2]), amode ? q.src : nullptr, q.out,
+                                       static_cast<const double*>(q.ca), static_cast<const double*>(q.cl),
+                                       static_cast<const double*>(q.cm), static_cast<const double*>(q.f), A,
+                                       TwoField2D{}, W);
+}
+
+}  // namespace
+
+int batch_reg_tiles(int nx, int nrows, int H, int* ntx) {
+    *ntx = tiles_x(nx - 1, H);
+    return *ntx * tiles_y(nrows, BNW * BR, H);
+}
+
+// Steps per tick for problems of the given interior sizes and steps per
+// application, from the model above: every tick costs its launches (25 us with
+// the counters and the CG kernels) and its rounds of tiles; the longest
+// application sets the number of ticks, all problems the work.
+int batch_reg_steps(const std::vector<BatchSize>& probs) {
+    constexpr int rows = BNW * BR;
+    int best = 4;
+    double tbest = 1e300;
+    for (int H = 4; H <= 10; ++H) {
+        double work = 0;
+        int ticks = 0, ntx;
+        const double inner = (64 - 2 * H) * (rows - 2 * H);
+        const double round = 3.0 + 0.04 * rows + 2.4e-3 * inner + H * (0.11 + 0.018 * rows);
+        for (const BatchSize& q : probs) {
+            const int n = (q.nsteps + H - 1) / H;
+            work += (double)batch_reg_tiles(q.nx, q.nrows, H, &ntx) * n;
+            ticks = std::max(ticks, n);
+        }
+        const double t = ticks * 25.0 + std::max(work / 256.0, (double)ticks) * round;
+        if (t < tbest) {
+            tbest = t;
+            best = H;
+        }
+    }
+    return best;
+}
+
+void launch_batch_tiles(bool force, int neighths, int H, hipStream_t s, const BProb2D* pr, const BState* st, int np,
+                        double sgn, int amode) {
+    if (neighths <= 0) return;
+    const dim3 grid((unsigned)(neighths * kXcds));
+    if (force)
+        hipLaunchKernelGGL(batch_tile2d_kernel<true>, grid, dim3(64 * BNW), 0, s, pr, st, np, H, sgn, amode);
+    else
+        hipLaunchKernelGGL(batch_tile2d_kernel<false>, grid, dim3(64 * BNW), 0, s, pr, st, np, H, sgn, amode);
 }
 
 }  // namespace elwh
