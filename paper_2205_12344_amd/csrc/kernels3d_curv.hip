@@ -22,7 +22,10 @@
 // (the 19-point footprint and the coefficients of the six face neighbours
 // are served by the caches) in straight-line code, so a wavefront has its
 // whole footprint in flight at once; one time step per launch.
+#include <algorithm>
+
 #include "elwh_internal.h"
+#include "lanes.h"
 #include "xcd.h"
 
 namespace elwh {
@@ -228,6 +231,250 @@ __global__ __launch_bounds__(64) void curv3d_kernel(const U* __restrict__ u, con
     }
 }
 
+// ---- FP64: marching workgroups that share the fluxes ---------------------------
+//
+// The gather above forms every node's contribution K^ab (D_b U) again at each of
+// the nodes that use it: 1353 instructions and 134 loads per node, 171 us per
+// step on the shell of 400 x 120 x 40 points, twice what its 216 B per update
+// take.  Here a node forms its contributions once and hands them over:
+//   F^a = sum_{b != a} K^ab D_b U     the cross flux along axis a,
+//   h^+-_a = K^aa (U_{p +- e_a} - U_p)   its halves of the two edge terms,
+// and along axis a it exports (to the node below and above it)
+//   X^-_a = F^a / (2 h_a) - h^-_a / (2 h_a^2),   X^+_a = -F^a / (2 h_a) - h^+_a / (2 h_a^2),
+// so L_p = sum_a [X^-_a of p + e_a, X^+_a of p - e_a, (h^-_a + h^+_a) / (2 h_a^2) of p itself].
+// The exports along an axis need only the differences along the other two, so
+// one halo node per side is enough.
+//
+// A workgroup of 8 wavefronts takes 8 rows (r) of 64 nodes (q), of which 6 x 62
+// are its own, and marches along s: q exports go by DPP, r exports through LDS
+// (two buffers, one barrier per plane), s exports stay in registers.  Every
+// array is read once per plane, one plane ahead.  The number of workgroups is
+// kept to one per CU (their registers fill it): the march is split along s only
+// as far as that allows.
+// On a free s face (trapezoid weight 1/2): dividing the row by the weight leaves
+// the in-plane terms as they are and doubles those along s; D_s is one-sided, and
+// the face's own F^s enters with its own coefficient.
+constexpr int M3_NW = 8, M3_Q = 62, M3_R = M3_NW - 2;
+
+struct V3d {
+    double x, y, z;
+};
+__device__ __forceinline__ double dot3(const V3d& a, const V3d& b) { return fma(a.x, b.x, fma(a.y, b.y, a.z * b.z)); }
+__device__ __forceinline__ V3d sub3(const V3d& a, const V3d& b) { return V3d{a.x - b.x, a.y - b.y, a.z - b.z}; }
+__device__ __forceinline__ V3d mul3(double s, const V3d& a) { return V3d{s * a.x, s * a.y, s * a.z}; }
+__device__ __forceinline__ V3d fma3(double s, const V3d& a, const V3d& b) {
+    return V3d{fma(s, a.x, b.x), fma(s, a.y, b.y), fma(s, a.z, b.z)};
+}
+__device__ __forceinline__ V3d from_left3(const V3d& a) {
+    return V3d{lane_from_left_z(a.x), lane_from_left_z(a.y), lane_from_left_z(a.z)};
+}
+__device__ __forceinline__ V3d from_right3(const V3d& a) {
+    return V3d{lane_from_right_z(a.x), lane_from_right_z(a.y), lane_from_right_z(a.z)};
+}
+
+struct Coef3 {
+    double l, m;       // lambda / J, mu / J
+    V3d g[3];
+};
+
+template <int MODE, bool FORCE>
+__global__ __launch_bounds__(64 * M3_NW) void curv3d_march_kernel(const double* __restrict__ u, const double* uprev,
+                                                                 double* unext, const double* __restrict__ xbase,
+                                                                 double* __restrict__ acc,
+                                                                 const double* __restrict__ ca,
+                                                                 const double* __restrict__ cl,
+                                                                 const double* __restrict__ cm, Metric3<double> G,
+                                                                 const double* __restrict__ f, ArgsC3 A, int tz) {
+    __shared__ double us[2][M3_NW][3][64];   // U of the plane being worked on, and of the next
+    __shared__ double xs[2][M3_NW][6][64];   // r exports: to the row below, to the row above
+    const int nbq = (A.nq - 1 + M3_Q - 1) / M3_Q, nbr = (A.nr - 1 + M3_R - 1) / M3_R;
+    const int nbs = (A.khi - A.klo + tz) / tz;
+    int t;
+    if (!xcd_tile((int)blockIdx.x, nbq * nbr * nbs, t)) return;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = (t % nbq) * M3_Q + lane;                 // own columns: lanes 1 .. 62
+    const int j = ((t / nbq) % nbr) * M3_R + w;            // own rows: wavefronts 1 .. 6
+    const int k0 = A.klo + (t / (nbq * nbr)) * tz, k1 = min(k0 + tz - 1, A.khi);
+    const bool in = i <= A.nq && j <= A.nr;
+    const bool own = lane >= 1 && lane <= M3_Q && w >= 1 && w <= M3_R && i <= A.nq - 1 && j <= A.nr - 1;
+    const bool unk = i >= 1 && i <= A.nq - 1 && j >= 1 && j <= A.nr - 1;   // unknown in its plane
+    const int64_t CS = A.CS, PS = A.PS, o0 = (int64_t)j * A.P + i;
+    const double cq = 0.5 / A.hq, cr = 0.5 / A.hr, cs = 0.5 / A.hs;
+    const double eq = 0.5 / (A.hq * A.hq), er = 0.5 / (A.hr * A.hr), es = 0.5 / (A.hs * A.hs);
+
+    auto ldu = [&](int k) {
+        V3d v{0.0, 0.0, 0.0};
+        if (in && k >= 0 && k <= A.ns) {
+            const int64_t o = o0 + k * PS;
+            v = V3d{u[o], u[o + CS], u[o + 2 * CS]};
+        }
+        return v;
+    };
+    auto ldc = [&](int k) {
+        Coef3 c{};
+        if (in && k >= 0 && k <= A.ns) {
+            const int64_t o = o0 + k * PS;
+            c.l = cl[o];
+            c.m = cm[o];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) c.g[a] = V3d{G.g[3 * a][o], G.g[3 * a + 1][o], G.g[3 * a + 2][o]};
+        }
+        return c;
+    };
+    auto put_u = [&](const V3d& v, int b) {
+        us[b][w][0][lane] = v.x;
+        us[b][w][1][lane] = v.y;
+        us[b][w][2][lane] = v.z;
+    };
+
+    // planes k0 - 1 (exports upwards only) .. k1 + 1 (exports downwards only)
+    const int ka = max(k0 - 1, 0), kb = min(k1 + 1, A.ns);
+    V3d um = ldu(ka - 1), uc = ldu(ka), up = ldu(ka + 1);
+    Coef3 c = ldc(ka);
+    V3d L{0.0, 0.0, 0.0};      // the row of plane kk - 1, all but the export from plane kk
+    V3d xup{0.0, 0.0, 0.0};    // s export of plane kk - 1 to plane kk
+    put_u(uc, ka & 1);
+    __syncthreads();
+
+    // centre values of a plane, loaded at the top of the iteration that finishes it
+    struct Centre3 {
+        double a;
+        V3d old, h, f;
+    };
+    auto ld_centre = [&](int k) {
+        Centre3 e{};
+        if (own && k >= k0 && k <= k1) {
+            const int64_t o = o0 + k * PS;
+            e.a = ca[o];
+            const double* hb = MODE == 0 ? acc : xbase;
+            if (hb) e.h = V3d{hb[o], hb[o + CS], hb[o + 2 * CS]};
+            if constexpr (MODE == 0) e.old = V3d{uprev[o], uprev[o + CS], uprev[o + 2 * CS]};
+            if constexpr (FORCE) e.f = V3d{f[o], f[o + CS], f[o + 2 * CS]};
+        }
+        return e;
+    };
+    auto finish = [&](int k, const Centre3& e, const V3d& uk, const V3d& down) {   // plane k, with the export of k + 1
+        const bool face = (A.free_lo && k == 0) || (A.free_hi && k == A.ns);
+        const V3d R = fma3(face ? 2.0 : 1.0, down, L);
+        if (own && k >= k0 && k <= k1) {
+            const double Lq[3] = {R.x, R.y, R.z}, uq[3] = {uk.x, uk.y, uk.z}, oq[3] = {e.old.x, e.old.y, e.old.z};
+            const double hq[3] = {e.h.x, e.h.y, e.h.z}, fq[3] = {e.f.x, e.f.y, e.f.z};
+            const int64_t o = o0 + k * PS;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const double s = FORCE ? Lq[q] - A.fc * fq[q] : Lq[q];
+                if constexpr (MODE == 0) {
+                    const double n = fma(e.a, s, fma(2.0, uq[q], -oq[q]));
+                    unext[o + q * CS] = n;
+                    acc[o + q * CS] = fma(A.w, n, hq[q]);
+                } else {
+                    const double n = fma(0.5 * e.a, s, uq[q]);
+                    unext[o + q * CS] = n;
+                    acc[o + q * CS] = fma(A.w, n, fma(A.w0, uq[q], hq[q]));
+                }
+            }
+        }
+    };
+
+    for (int kk = ka; kk <= kb; ++kk) {
+        const int b = kk & 1;
+        const Centre3 e = ld_centre(kk - 1);
+        const V3d upp = ldu(kk + 2);
+        const Coef3 cn = kk < kb ? ldc(kk + 1) : Coef3{};
+        const bool flo = A.free_lo && kk == 0, fhi = A.free_hi && kk == A.ns;
+        const bool plane = kk >= A.klo && kk <= A.khi;   // unknown planes
+        const double mask = unk && plane ? 1.0 : 0.0;
+        // differences: clamped across a free face, where D_s doubles
+        const int wm = w > 0 ? w - 1 : w, wn = w < M3_NW - 1 ? w + 1 : w;   // (halo rows need no D_r)
+        const V3d rm{us[b][wm][0][lane], us[b][wm][1][lane], us[b][wm][2][lane]};
+        const V3d rp{us[b][wn][0][lane], us[b][wn][1][lane], us[b][wn][2][lane]};
+        const V3d qm = from_left3(uc), qp = from_right3(uc);
+        const V3d sm = flo ? uc : um, sp = fhi ? uc : up;
+        const double cs2 = (flo || fhi ? 2.0 : 1.0) * cs;
+        const V3d dq = mul3(cq, sub3(qp, qm)), dr = mul3(cr, sub3(rp, rm)), ds = mul3(cs2, sub3(sp, sm));
+        // cross fluxes: F^a = l G_a sum_{b != a} G_b . d_b + m sum_{b != a} (G_b (G_a . d_b) + (G_a . G_b) d_b)
+        const V3d &gq = c.g[0], &gr = c.g[1], &gs = c.g[2];
+        const double qq = dot3(gq, dq), rr = dot3(gr, dr), ss = dot3(gs, ds);
+        const double Sqr = dot3(gq, gr), Sqs = dot3(gq, gs), Srs = dot3(gr, gs);
+        const double lm = mask * c.l, mm = mask * c.m;
+        auto cross = [&](const V3d& ga, double tr, const V3d& gb, double gab, double Sab, const V3d& db, const V3d& gc,
+                         double gac, double Sac, const V3d& dc) {
+            V3d v = mul3(gab, gb);
+            v = fma3(Sab, db, v);
+            v = fma3(gac, gc, v);
+            v = fma3(Sac, dc, v);
+            return fma3(lm * tr, ga, mul3(mm, v));
+        };
+        const V3d Fq = cross(gq, rr + ss, gr, dot3(gq, dr), Sqr, dr, gs, dot3(gq, ds), Sqs, ds);
+        const V3d Fr = cross(gr, qq + ss, gq, dot3(gr, dq), Sqr, dq, gs, dot3(gr, ds), Srs, ds);
+        const V3d Fs = cross(gs, qq + rr, gq, dot3(gs, dq), Sqs, dq, gr, dot3(gs, dr), Srs, dr);
+        // halves of the edge terms, K^aa d = (l + m) G_a (G_a . d) + m |G_a|^2 d, over 2 h_a^2
+        auto half = [&](const V3d& g, double e, double S, const V3d& d) {
+            return fma3(e * (c.l + c.m) * dot3(g, d), g, mul3(e * c.m * S, d));
+        };
+        const double Sqq = dot3(gq, gq), Srr = dot3(gr, gr), Sss = dot3(gs, gs);
+        const V3d hqm = half(gq, eq, Sqq, sub3(qm, uc)), hqp = half(gq, eq, Sqq, sub3(qp, uc));
+        const V3d hrm = half(gr, er, Srr, sub3(rm, uc)), hrp = half(gr, er, Srr, sub3(rp, uc));
+        const V3d hsm = half(gs, es, Sss, sub3(sm, uc)), hsp = half(gs, es, Sss, sub3(sp, uc));
+        // r exports and the next plane's U, then the barrier
+        {
+            const V3d xm = fma3(cr, Fr, mul3(-1.0, hrm)), xp = fma3(-cr, Fr, mul3(-1.0, hrp));
+            double(&x)[6][64] = xs[b][w];
+            x[0][lane] = xm.x;
+            x[1][lane] = xm.y;
+            x[2][lane] = xm.z;
+            x[3][lane] = xp.x;
+            x[4][lane] = xp.y;
+            x[5][lane] = xp.z;
+        }
+        put_u(up, b ^ 1);
+        // q and s exports meanwhile
+        const V3d xqm = fma3(cq, Fq, mul3(-1.0, hqm)), xqp = fma3(-cq, Fq, mul3(-1.0, hqp));
+        const V3d xsm = fma3(cs, Fs, mul3(-1.0, hsm)), xsp = fma3(-cs, Fs, mul3(-1.0, hsp));
+        const V3d fromq = from_right3(xqm), fromq2 = from_left3(xqp);
+        const double iw = flo || fhi ? 2.0 : 1.0;
+        V3d own_s = fma3(1.0, hsm, hsp);
+        if (flo) own_s = fma3(cs, Fs, own_s);    // -(D_s)_pp w_p = 1 / (2 h_s) on the lower face
+        if (fhi) own_s = fma3(-cs, Fs, own_s);
+        V3d Ln{hqm.x + hqp.x + hrm.x + hrp.x + fromq.x + fromq2.x, hqm.y + hqp.y + hrm.y + hrp.y + fromq.y + fromq2.y,
+               hqm.z + hqp.z + hrm.z + hrp.z + fromq.z + fromq2.z};
+        Ln = fma3(iw, V3d{own_s.x + xup.x, own_s.y + xup.y, own_s.z + xup.z}, Ln);
+        __syncthreads();
+        {
+            const double(&em)[6][64] = xs[b][wm];   // from the row below: its upward export
+            const double(&ep)[6][64] = xs[b][wn];   // from the row above: its downward export
+            Ln.x += em[3][lane] + ep[0][lane];
+            Ln.y += em[4][lane] + ep[1][lane];
+            Ln.z += em[5][lane] + ep[2][lane];
+        }
+        finish(kk - 1, e, um, xsm);
+        L = Ln;
+        xup = xsp;
+        um = uc;
+        uc = up;
+        up = upp;
+        c = cn;
+    }
+    // the last plane where nothing lies above it (a free face)
+    if (kb == k1) finish(k1, ld_centre(k1), um, V3d{0.0, 0.0, 0.0});
+}
+
+template <int MODE>
+static void launch_march3(bool force, const ArgsC3& A, hipStream_t s, const double* u, const double* uprev,
+                          double* unext, const double* xbase, double* acc, const double* ca, const double* cl,
+                          const double* cm, const Metric3<double>& G, const double* f) {
+    const int nb = ((A.nq - 1 + M3_Q - 1) / M3_Q) * ((A.nr - 1 + M3_R - 1) / M3_R), np = A.khi - A.klo + 1;
+    // as many chunks along s as keep to one workgroup per CU, of at least 4 planes
+    const int chunks = std::max(1, std::min(256 / nb, np / 4)), tz = (np + chunks - 1) / chunks;
+    const dim3 grid((unsigned)xcd_grid(nb * ((np + tz - 1) / tz)));
+    if (force)
+        hipLaunchKernelGGL((curv3d_march_kernel<MODE, true>), grid, dim3(64 * M3_NW), 0, s, u, uprev, unext, xbase, acc,
+                           ca, cl, cm, G, f, A, tz);
+    else
+        hipLaunchKernelGGL((curv3d_march_kernel<MODE, false>), grid, dim3(64 * M3_NW), 0, s, u, uprev, unext, xbase,
+                           acc, ca, cl, cm, G, f, A, tz);
+}
+
 bool tile_valid_curv3(bool fp32, int V, int TY) {
     (void)fp32;
     return V == 1 && TY == 4;
@@ -280,8 +527,7 @@ void run_filter_curv3d(elwh_ctx* c, const double* x, bool with_force, bool amode
         for (int q = 0; q < 9; ++q) G.g[q] = c->cg[q];
         double *b0 = c->s64[0], *b1 = c->s64[1];
         prof_mark(c, 0);
-        launch_c3<double, double, 1>(with_force, false, A, s, x, nullptr, b1, amode ? x : nullptr, nullptr, acc, lo,
-                                     c->ca, c->cl, c->cm, G, c->f64);
+        launch_march3<1>(with_force, A, s, x, nullptr, b1, amode ? x : nullptr, acc, c->ca, c->cl, c->cm, G, c->f64);
         prof_mark(c, 1);
         const double* prev = x;
         double* cur = b1;
@@ -289,8 +535,7 @@ void run_filter_curv3d(elwh_ctx* c, const double* x, bool with_force, bool amode
             double* nxt = (n == 1) ? b0 : const_cast<double*>(prev);
             A.w = sgn * c->w[n + 1];
             A.fc = c->cosn[n];
-            launch_c3<double, double, 0>(with_force, false, A, s, cur, prev, nxt, nullptr, nullptr, acc, lo, c->ca,
-                                         c->cl, c->cm, G, c->f64);
+            launch_march3<0>(with_force, A, s, cur, prev, nxt, nullptr, acc, c->ca, c->cl, c->cm, G, c->f64);
             prev = cur;
             cur = nxt;
         }
