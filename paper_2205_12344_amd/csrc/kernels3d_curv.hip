@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64) void curv3d_kernel(const U* __restrict__ u, con
     }
 }
 
-// ---- FP64: marching workgroups that share the fluxes ---------------------------
+// ---- FP64, large grids: marching workgroups that share the fluxes ----------------
 //
 // The gather above forms every node's contribution K^ab (D_b U) again at each of
 // the nodes that use it: 1353 instructions and 134 loads per node, 171 us per
@@ -459,13 +459,30 @@ __global__ __launch_bounds__(64 * M3_NW) void curv3d_march_kernel(const double* 
     if (kb == k1) finish(k1, ld_centre(k1), um, V3d{0.0, 0.0, 0.0});
 }
 
+// The march costs a few planes' latency before its first store, the gather none:
+// 8.6 k nodes 9.3 against 5.3 us per step, 63 k 10.2 against 8.7, 228 k 18.1
+// against 28.6, 1.88 M 95 against 171.
+static bool march3_pays(const ArgsC3& A) {
+    return (int64_t)(A.nq - 1) * (A.nr - 1) * (A.khi - A.klo + 1) >= 80000;
+}
+
 template <int MODE>
 static void launch_march3(bool force, const ArgsC3& A, hipStream_t s, const double* u, const double* uprev,
                           double* unext, const double* xbase, double* acc, const double* ca, const double* cl,
                           const double* cm, const Metric3<double>& G, const double* f) {
     const int nb = ((A.nq - 1 + M3_Q - 1) / M3_Q) * ((A.nr - 1 + M3_R - 1) / M3_R), np = A.khi - A.klo + 1;
-    // as many chunks along s as keep to one workgroup per CU, of at least 4 planes
-    const int chunks = std::max(1, std::min(256 / nb, np / 4)), tz = (np + chunks - 1) / chunks;
+    // Chunks along s: one workgroup per CU at a time, so the fewest rounds times
+    // planes (a chunk works on two planes more than it owns).  The shell's 140
+    // columns of 40 planes in one round use 140 of 256 CUs: 124 us per step; in
+    // five chunks (three rounds of 10 planes) 95.
+    int tz = np, best = 1 << 30;
+    for (int z = 1; z <= np; ++z) {
+        const int cost = (nb * ((np + z - 1) / z) + 255) / 256 * (z + 2);
+        if (cost <= best) {
+            best = cost;
+            tz = z;
+        }
+    }
     const dim3 grid((unsigned)xcd_grid(nb * ((np + tz - 1) / tz)));
     if (force)
         hipLaunchKernelGGL((curv3d_march_kernel<MODE, true>), grid, dim3(64 * M3_NW), 0, s, u, uprev, unext, xbase, acc,
@@ -527,7 +544,12 @@ void run_filter_curv3d(elwh_ctx* c, const double* x, bool with_force, bool amode
         for (int q = 0; q < 9; ++q) G.g[q] = c->cg[q];
         double *b0 = c->s64[0], *b1 = c->s64[1];
         prof_mark(c, 0);
-        launch_march3<1>(with_force, A, s, x, nullptr, b1, amode ? x : nullptr, acc, c->ca, c->cl, c->cm, G, c->f64);
+        const bool march = march3_pays(A);
+        if (march)
+            launch_march3<1>(with_force, A, s, x, nullptr, b1, amode ? x : nullptr, acc, c->ca, c->cl, c->cm, G, c->f64);
+        else
+            launch_c3<double, double, 1>(with_force, false, A, s, x, nullptr, b1, amode ? x : nullptr, nullptr, acc, lo,
+                                         c->ca, c->cl, c->cm, G, c->f64);
         prof_mark(c, 1);
         const double* prev = x;
         double* cur = b1;
@@ -535,7 +557,11 @@ void run_filter_curv3d(elwh_ctx* c, const double* x, bool with_force, bool amode
             double* nxt = (n == 1) ? b0 : const_cast<double*>(prev);
             A.w = sgn * c->w[n + 1];
             A.fc = c->cosn[n];
-            launch_march3<0>(with_force, A, s, cur, prev, nxt, nullptr, acc, c->ca, c->cl, c->cm, G, c->f64);
+            if (march)
+                launch_march3<0>(with_force, A, s, cur, prev, nxt, nullptr, acc, c->ca, c->cl, c->cm, G, c->f64);
+            else
+                launch_c3<double, double, 0>(with_force, false, A, s, cur, prev, nxt, nullptr, nullptr, acc, lo, c->ca,
+                                             c->cl, c->cm, G, c->f64);
             prev = cur;
             cur = nxt;
         }

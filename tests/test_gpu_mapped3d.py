@@ -220,3 +220,22 @@ def test_shell_at_benchmark_size_properties(E):
     err = _rel(c32.apply_A(a).cpu().numpy(), Aa.cpu().numpy())
     _say("shell fp32 vs fp64", err, "bound", fp32_bound(nt))
     assert err <= fp32_bound(nt)
+
+
+@pytest.mark.parametrize("n,bc", [
+    ((125, 61, 12), (0, 0, 0, 0, 1, 1)),      # whole tiles of 62 x 6 nodes, 13 free-ended planes
+    ((126, 62, 13), (0, 0, 0, 0, 0, 0)),      # one node more than whole tiles each way
+    ((62, 43, 34), (0, 0, 0, 0, 0, 1)),       # one tile across, thick in s
+    ((66, 44, 32), (0, 0, 0, 0, 1, 0)),
+])
+def test_marching_kernel_matches_oracle(E, n, bc):
+    """FP64 grids of 80 000 and more unknown nodes, which march along s: filter
+    with forcing and A_h against the oracle to the FP64 bar."""
+    data, op, wh = _setup(n, bc, (1.9, 1.1), 31, omega=9.0)
+    prob = op.prob
+    rng = np.random.default_rng(8)
+    u0, f = (rng.standard_normal(prob.field_shape) * prob.unknown_mask() for _ in range(2))
+    ctx = E.MappedContext3(*data, 9.0, bc=bc)
+    ref = wh.apply_filter(prob.gather(u0), prob.gather(f))
+    assert _rel(prob.gather(ctx.apply_filter(u0, f).cpu().numpy()), ref) <= FP64_TOL
+    assert _rel(prob.gather(ctx.apply_A(u0).cpu().numpy()), wh.apply_A(prob.gather(u0))) <= FP64_TOL
