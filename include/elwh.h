@@ -220,9 +220,9 @@ elwh_status elwh_create(const elwh_grid* grid, const double* rho, const double* 
  * Dirichlet; each r side is Dirichlet or traction-free, closed from the same
  * energy with trapezoid weight 1/2 on its nodes and q-edges and the
  * one-sided r difference in its cross terms (M weights rho J / 2 there).
- * Every time step is one launch (opts->fuse is ignored).  x, y, rho, lam, mu
- * are DEVICE pointers, copied.  Errors: ELWH_ERR_ARG (also for a map with
- * J <= 0 at some node, i.e. folded or left-handed, or non-finite
+ * opts->fuse is ignored: FP64 stepping takes several steps per launch unless a
+ * tiling is set, FP32 stepping one.  x, y, rho, lam, mu are DEVICE pointers,
+ * copied.  Errors: ELWH_ERR_ARG (also for a map with J <= 0 at some node, i.e. folded or left-handed, or non-finite
  * coordinates), ELWH_ERR_ALLOC, ELWH_ERR_HIP; on error *out is NULL.  The
  * batched solver does not take mapped grids.
  */
@@ -476,9 +476,9 @@ elwh_status elwh_profile_read(elwh_ctx* ctx, double* step_ms, int* nstep, double
  * (2, 4, 6) x (8, 16, 32, 64) for two-step launches (fuse >= 2; the workgroup
  * adds two halo rows), where vec = 1 with rows 4 to 32 makes every step a
  * single-step launch (the FP64 choice on large cubes).  The tiling changes
- * speed only, never results.  On 2-D Cartesian grids it is that of the marching
- * kernels, which FP32 stepping, opts.fuse < 4 and large grids use; setting an FP64
- * tiling there makes the context use them.
+ * speed only, never results.  On 2-D grids it is that of the marching
+ * kernels, which FP32 stepping and, on Cartesian grids, opts.fuse < 4 and large
+ * grids use; setting an FP64 tiling there makes the context use them.
  * elwh_autotune times every supported tiling on reps operator applications
  * (HIP events), in three round-robin passes, and keeps the tiling with the
  * fastest pass (contexts with impedance faces time the two-field step);

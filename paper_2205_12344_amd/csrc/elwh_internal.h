@@ -288,11 +288,17 @@ void launch_step3d_k2(int RB, int TZ, bool force, bool comp, hipStream_t s, cons
 // Cartesian context takes (H = 0: none, the marching kernels), and such an
 // application.
 TileShape tile2d_shape(const elwh_ctx* c, bool two);
+Tile2D tile2d_args(const elwh_ctx* c, const TileShape& t);
+// The two FP64 state buffers that are neither a nor b.
+void other_two(const elwh_ctx* c, const double* a, const double* b, double** o);
 void run_filter_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool with_force, bool amode, double* out);
 void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x0, const double* z1, bool with_force,
                                 bool amode, double s_in, double s_out, double* out0, double* out1);
 bool tile_valid_curv(bool fp32, int V, int TY);
 bool tile_valid_curv3(bool fp32, int V, int TY);
+// The same on a mapped 2-D grid (kernels2d_curv_tile.hip): shape, none if a tiling was asked for.
+TileShape curv_tile_shape(const elwh_ctx* c);
+void run_filter_curv_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool with_force, bool amode, double* out);
 // One filter application on a mapped 2-D grid (kernels2d_curv.hip).
 void run_filter_curv2d(elwh_ctx* c, const double* x, bool with_force, bool amode, bool fp32, double* out);
 // One filter application on a mapped 3-D grid (kernels3d_curv.hip).

@@ -395,6 +395,11 @@ bool tile_valid_curv(bool /*fp32*/, int V, int TY) { return (V == 1 || V == 2) &
 // single steps, u^{n+1} over u^{n-1} (FP64: u^0 is read from x itself, so
 // the first full step writes a third state buffer).
 void run_filter_curv2d(elwh_ctx* c, const double* x, bool with_force, bool amode, bool fp32, double* out) {
+    const TileShape ts = fp32 ? TileShape() : curv_tile_shape(c);
+    if (ts.H) {
+        run_filter_curv_tile2d(c, ts, x, with_force, amode, out);
+        return;
+    }
     hipStream_t s = c->stream;
     Args2D A = make_args2d(c);
     const int nrows = A.jhi - A.jlo + 1;

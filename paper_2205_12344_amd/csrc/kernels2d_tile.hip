@@ -418,9 +418,7 @@ TileShape tile2d_shape(const elwh_ctx* c, bool two) {
     return tile2d_pick(c->L.nx, rows, c->plan.nt * c->opts.periods + (two ? 1 : 0), two);
 }
 
-namespace {
-
-Tile2D tile_args(const elwh_ctx* c, const TileShape& t) {
+Tile2D tile2d_args(const elwh_ctx* c, const TileShape& t) {
     Tile2D A{};
     A.nx = c->L.nx;
     A.ny = c->L.ny;
@@ -437,19 +435,16 @@ Tile2D tile_args(const elwh_ctx* c, const TileShape& t) {
     return A;
 }
 
-// The two state buffers that are neither a nor b.
 void other_two(const elwh_ctx* c, const double* a, const double* b, double** o) {
     int k = 0;
     for (double* p : c->s64)
         if (k < 2 && p != a && p != b) o[k++] = p;
 }
 
-}  // namespace
-
 void run_filter_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool with_force, bool amode, double* out) {
     const int nsteps = c->plan.nt * c->opts.periods;
     const double sgn = amode ? -1.0 : 1.0;
-    Tile2D A = tile_args(c, t);
+    Tile2D A = tile2d_args(c, t);
     A.w0 = sgn * c->w[0];
     const double *cur = x, *prev = nullptr;
     prof_mark(c, 0);
@@ -477,7 +472,7 @@ void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x
                                 bool amode, double s_in, double s_out, double* out0, double* out1) {
     const int N = c->plan.nt * c->opts.periods;   // and one step more, for the velocity of the last level
     const double sgn = amode ? -1.0 : 1.0, dt = c->plan.dt;
-    Tile2D A = tile_args(c, t);
+    Tile2D A = tile2d_args(c, t);
     A.w0 = sgn * c->w[0];
     TwoField2D D{};
     D.base1 = amode ? z1 : nullptr;

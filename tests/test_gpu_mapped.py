@@ -348,3 +348,32 @@ def test_mapped_k_period_cg_matches_oracle(E, K):
     _say("mapped K-period CG", K, "iters", info["iters"], "oracle", res.iters)
     assert abs(info["iters"] - res.iters) <= 1
     assert _rel(prob.gather(v.cpu().numpy()), res.x) <= 1e-8
+
+
+# ---- several steps per launch (no tiling asked for) -----------------------------
+# sizes at and beside the tiles' inner columns and rows and their wavefronts' rows,
+# N_T at and beside multiples of the steps per launch; the largest fills more
+# than one round of the CUs
+@pytest.mark.parametrize("kind,nq,nr,bc,periods", [
+    ("warped", 2, 2, (0, 0, 0, 0), 1), ("ring", 3, 7, (0, 0, 1, 1), 1), ("quarter", 41, 8, (0, 0, 0, 1), 1),
+    ("warped", 45, 32, (0, 0, 1, 0), 1), ("half", 51, 27, (0, 0, 0, 0), 3), ("ring", 89, 33, (0, 0, 1, 1), 1),
+    ("warped", 65, 64, (0, 0, 1, 1), 1), ("ring", 60, 41, (0, 0, 0, 1), 2), ("quarter", 700, 610, (0, 0, 1, 1), 1),
+])
+def test_mapped_register_tiles(E, kind, nq, nr, bc, periods):
+    x, y = _grid_bc(kind, nq, nr, seed=nq)
+    rho, lam, mu = inputs.media_mapped(x, y, seed=nq + 3 * nr)
+    op = MappedOperator(x, y, rho, lam, mu, bc=bc)
+    om = 6.3 if nq < 500 else 400.0
+    wh = S.WaveHoltz(op, om, periods=periods)
+    prob = op.prob
+    rng = np.random.default_rng(23)
+    u0, f = (rng.standard_normal(prob.field_shape) for _ in range(2))   # known nodes' values are ignored
+    gu, gf = prob.gather(u0), prob.gather(f)
+    ctx = E.MappedContext(x, y, rho, lam, mu, om, bc=bc, periods=periods)
+    assert ctx.info()["nt"] == wh.nt
+    got, gotA = ctx.apply_filter(u0, f).cpu().numpy(), ctx.apply_A(u0).cpu().numpy()
+    _say("mapped register tiles", kind, nq, nr, bc, "nt", wh.nt)
+    assert _rel(prob.gather(got), wh.apply_filter(gu, gf)) <= FP64_TOL
+    assert _rel(prob.gather(gotA), gu - wh.apply_filter(gu)) <= FP64_TOL
+    known = prob.scatter(np.ones(op.ndof)) == 0
+    assert not np.any(got[known]) and not np.any(gotA[known])
