@@ -106,8 +106,9 @@ typedef struct {
     int autotune;      /* 1 (default): pick the step-kernel tiling by timing at create */
     int fuse;          /* time steps per step-kernel launch: 2-D Cartesian 1 to 4,
                           3-D Cartesian 1 or 2 (larger values act as 2, and
-                          the tiling may still choose single steps); default 4;
-                          mapped grids always step singly.  In FP64 on 2-D
+                          the tiling may still choose single steps, which
+                          FP64 takes where no tiling was asked for); default 4;
+                          mapped grids ignore it.  In FP64 on 2-D
                           Cartesian grids 4 also lets the library take more
                           (register tiles of up to 12 steps, up to about
                           2000^2 nodes; the two-field step at every size)
@@ -476,9 +477,9 @@ elwh_status elwh_profile_read(elwh_ctx* ctx, double* step_ms, int* nstep, double
  * (2, 4, 6) x (8, 16, 32, 64) for two-step launches (fuse >= 2; the workgroup
  * adds two halo rows), where vec = 1 with rows 4 to 32 makes every step a
  * single-step launch (the FP64 choice on large cubes).  The tiling changes
- * speed only, never results.  On 2-D grids it is that of the marching
- * kernels, which FP32 stepping and, on Cartesian grids, opts.fuse < 4 and large
- * grids use; setting an FP64 tiling there makes the context use them.
+ * speed only, never results.  It is that of the kernels which FP32 stepping
+ * and, on 2-D Cartesian grids, opts.fuse < 4 and large grids use; setting an
+ * FP64 tiling makes FP64 stepping use them on 2-D grids and 3-D Cartesian ones.
  * elwh_autotune times every supported tiling on reps operator applications
  * (HIP events), in three round-robin passes, and keeps the tiling with the
  * fastest pass (contexts with impedance faces time the two-field step);

@@ -294,6 +294,12 @@ void other_two(const elwh_ctx* c, const double* a, const double* b, double** o);
 void run_filter_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool with_force, bool amode, double* out);
 void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x0, const double* z1, bool with_force,
                                 bool amode, double s_in, double s_out, double* out0, double* out1);
+struct Args3D;
+// The FP64 marching step on 3-D Cartesian grids (kernels3d_march.hip), and whether it is taken.
+bool march3d_pays(const elwh_ctx* c);
+void launch_march3d(bool start, bool force, const Args3D& A, hipStream_t s, const double* u, const double* uprev,
+                    double* unext, const double* base, double* acc, const double* ca, const double* cl,
+                    const double* cm, const double* f);
 bool tile_valid_curv(bool fp32, int V, int TY);
 bool tile_valid_curv3(bool fp32, int V, int TY);
 // The same on a mapped 2-D grid (kernels2d_curv_tile.hip): shape, none if a tiling was asked for.

@@ -337,7 +337,23 @@ void run_filter_3d(elwh_ctx* c, const double* x, bool with_force, bool amode, bo
     A.w0 = sgn * c->w[0];
     A.w = sgn * c->w[1];
     A.fc = c->cosn[0];
-    if (!fp32) {
+    if (!fp32 && march3d_pays(c)) {
+        prof_mark(c, 0);
+        launch_march3d(true, with_force, A, s, x, nullptr, c->s64[1], amode ? x : nullptr, acc, c->ca, c->cl, c->cm,
+                       c->f64);
+        prof_mark(c, 1);
+        // u^0 is the caller's x (read only): step 1 writes the other buffer, every
+        // later one overwrites u^{n-1}
+        const double *prev = x, *cur = c->s64[1];
+        for (int n = 1; n < nsteps; ++n) {
+            double* nxt = n == 1 ? c->s64[0] : const_cast<double*>(prev);
+            A.w = sgn * c->w[n + 1];
+            A.fc = c->cosn[n];
+            launch_march3d(false, with_force, A, s, cur, prev, nxt, nullptr, acc, c->ca, c->cl, c->cm, c->f64);
+            prev = cur;
+            cur = nxt;
+        }
+    } else if (!fp32) {
         double* b1 = c->s64[1];
         prof_mark(c, 0);
         launch3_z<double, double, 1>(RB1, TZ, with_force, false, A, s, x, nullptr, b1, amode ? x : nullptr, nullptr,
