@@ -98,6 +98,23 @@ def phase_bytes(dim, tag, fuse, nt, nodes):
     return b, len(ks)
 
 
+def register_tile(nx, nrows, nsteps):
+    """The library's register tiles for FP64 steps of a 2-D Cartesian grid
+    (tile2d_pick in kernels2d_tile.hip): (wavefronts, rows each, steps per
+    launch), by the same model of an application's time."""
+    best = None
+    for nw, r in ((4, 4), (8, 3), (8, 4)):
+        rows = nw * r
+        for h in range(3, min(12, rows // 2 - 1) + 1):
+            tiles = -(-(nx - 1) // (64 - 2 * h)) * -(-nrows // (rows - 2 * h))
+            rounds, inner = -(-tiles // 256), (64 - 2 * h) * (rows - 2 * h)
+            t = (-(-nsteps // h) * (1.5 + rounds * (3.0 + 0.04 * rows + 2.4e-3 * inner))
+                 + rounds * nsteps * (0.11 + 0.018 * rows))
+            if best is None or t < best[0]:
+                best = (t, nw, r, h)
+    return best[1:]
+
+
 def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
@@ -138,6 +155,7 @@ def read_traffic(kernel_tag, tile, family="2d"):
 # the hash of its family's sources at the time of collection)
 KERNEL_SOURCES = {
     "2d": ("kernels2d.hip", "kernels2d_multi.hip", "step2d_common.h", "xcd.h", "lanes.h"),
+    "2dtile": ("kernels2d_tile.hip", "step2d_common.h", "xcd.h", "lanes.h"),
     "3d": ("kernels3d.hip", "kernels3d_k2.hip", "step3d_common.h", "xcd.h", "lanes.h"),
 }
 
@@ -192,10 +210,15 @@ def mapped_rates(elwh, inputs, napply=3):
         bb = BYTES_PER_LUP_MAPPED[tag]
         t = ctx.get_tile(elwh.FP64 if tag == "f64" else elwh.FP32_STEP)
         out[tag] = {"workload": MAPPED_WORKLOAD, "cells": [x.shape[1] - 1, x.shape[0] - 1], "omega": om,
-                    "nt": ctx.info()["nt"], "tile": list(t), "kernel": "curv2d_kernel",
-                    "step_kernel_us": round(1e6 * avg_s, 3), "glup_s_kernel": round(nodes / avg_s / 1e9, 3),
-                    "bytes_per_lup": bb, "achieved_GBs": round(bb * nodes / avg_s / 1e9, 1),
-                    "frac": round(bb * nodes / avg_s / 1e9 / HBM_PEAK_GBS, 4)}
+                    "nt": ctx.info()["nt"],
+                    "step_kernel_us": round(1e6 * avg_s, 3), "glup_s_kernel": round(nodes / avg_s / 1e9, 3)}
+        if tag == "f64":   # several steps per launch: lattice updates priced at a single step's bytes
+            out[tag].update({"kernel": "curv_tile_kernel", "effective_bytes_per_lup": bb,
+                             "effective_frac": round(bb * nodes / avg_s / 1e9 / HBM_PEAK_GBS, 4)})
+        else:
+            out[tag].update({"kernel": "curv2d_kernel", "tile": list(t), "bytes_per_lup": bb,
+                             "achieved_GBs": round(bb * nodes / avg_s / 1e9, 1),
+                             "frac": round(bb * nodes / avg_s / 1e9 / HBM_PEAK_GBS, 4)})
         log(f"mapped {tag}: {out[tag]}")
         ctx.close()
     return out
@@ -217,11 +240,11 @@ def twofield_rates(elwh, inputs, napply=3, solve=True):
     ctx.profile_enable(False)
     avg_s = p["step_ms"] * 1e-3 / max(p["nstep"], 1)
     bb = BYTES_PER_LUP_TWOFIELD
-    out = {"workload": TWOFIELD_WORKLOAD, "nt": ctx.info()["nt"], "tile": list(ctx.get_tile(elwh.FP64)),
-           "kernel": "damped2d_kernel", "step_kernel_us": round(1e6 * avg_s, 3),
-           "glup_s_kernel": round(nodes / avg_s / 1e9, 3), "bytes_per_lup": bb,
-           "achieved_GBs": round(bb * nodes / avg_s / 1e9, 1),
-           "frac": round(bb * nodes / avg_s / 1e9 / HBM_PEAK_GBS, 4)}
+    # several steps per launch: lattice updates priced at a single step's bytes
+    out = {"workload": TWOFIELD_WORKLOAD, "nt": ctx.info()["nt"],
+           "kernel": "tile2d_kernel (two fields)", "step_kernel_us": round(1e6 * avg_s, 3),
+           "glup_s_kernel": round(nodes / avg_s / 1e9, 3), "effective_bytes_per_lup": bb,
+           "effective_frac": round(bb * nodes / avg_s / 1e9 / HBM_PEAK_GBS, 4)}
     if solve:
         # GMRES(30) to 1e-8 on the same workload, from zero
         f = torch.tensor(case.f, device="cuda")
@@ -536,7 +559,8 @@ def mapped3_rates(elwh, napply=2):
         p = kernel_rate(ctx, napply)
         avg_s = p["step_ms"] * 1e-3 / max(p["nstep"], 1)
         bb = BYTES_PER_LUP_MAPPED3[tag]
-        out[tag] = {"workload": MAPPED3_WORKLOAD, "nt": ctx.info()["nt"], "kernel": "curv3d_kernel",
+        out[tag] = {"workload": MAPPED3_WORKLOAD, "nt": ctx.info()["nt"],
+                    "kernel": "curv3d_march_kernel" if tag == "f64" else "curv3d_kernel",
                     "step_kernel_us": round(1e6 * avg_s, 3), "glup_s_kernel": round(nodes / avg_s / 1e9, 3),
                     "bytes_per_lup": bb, "achieved_GBs": round(bb * nodes / avg_s / 1e9, 1),
                     "frac": round(bb * nodes / avg_s / 1e9 / HBM_PEAK_GBS, 4)}
@@ -816,55 +840,60 @@ def main():
     ctx = elwh.context_from_case(case)
     info = ctx.info()
     nt = info["nt"]
-    tv, tr = ctx.get_tile(elwh.FP64)
     ctx.cg_begin(case.f)
     el, prof = time_cg(ctx, args.steps, args.warmup)
     lup_per_step = nt * nodes
     value = lup_per_step * args.steps / el
     ms_per_step = 1e3 * el / args.steps
-    # every application runs N_T - 1 steps after the half step: K-step
-    # launches and, when K does not divide N_T - 1, one shorter launch
+    # every application is ceil(N_T / H) register-tile launches of up to H steps,
+    # the start included; each reads u^n, u^{n-1}, the accumulator and the three
+    # coefficients once and writes two levels and the accumulator (the first has no
+    # u^{n-1} to read)
     napp = prof["nstep"] // max(nt - 1, 1)
     fuse = elwh.default_opts().fuse
-    bytes_app, launches_app = phase_bytes(2, "f64", fuse, nt, nodes)
-    phase_gbs = bytes_app * napp / (prof["step_ms"] * 1e-3) / 1e9
-    # the dominant kernel alone: the same workload and tiling with N_T
-    # rounded up so that K divides N_T - 1 (the weights change, the kernel's
-    # work per launch does not); HIP events on the context's stream
-    nt_k = fuse * ((nt - 1 + fuse - 1) // fuse) + 1
+    nrows = nodes // (case.n[0] - 1)
+    nw, nr, h = register_tile(case.n[0], nrows, nt)
+    bytes_launch = BYTES_PER_MULTI_LAUNCH["f64"] * nodes
+    phase_gbs = (-(-nt // h) * bytes_launch - 16 * nodes) * napp / (prof["step_ms"] * 1e-3) / 1e9
+    # the dominant kernel alone: the same workload with N_T rounded up to a
+    # multiple of its H (the weights change, the kernel's work per launch does
+    # not); HIP events on the context's stream
+    nt_k = h * -(-nt // h)
+    nw, nr, h = register_tile(case.n[0], nrows, nt_k)
     ck = elwh.context_from_case(case, nt=nt_k, autotune=0)
-    ck.set_tile(elwh.FP64, tv, tr)
     pk = kernel_rate(ck, 10)
     ck.close()
-    step_avg_ms = pk["step_ms"] / max(pk["nstep"] // fuse, 1)
-    achieved = BYTES_PER_MULTI_LAUNCH["f64"] * nodes / (step_avg_ms * 1e-3) / 1e9
-    traffic = read_traffic(f"multi2d_k{fuse}_f64_square1024", (tv, tr))
-    log(f"tile V={tv} TY={tr}")
-    log(f"fp64: {ms_per_step:.3f} ms/step, {value / 1e9:.2f} GLUP/s, {fuse}-step kernel {1e3 * step_avg_ms:.2f} us "
-        f"({pk['nstep'] // fuse} launches at N_T = {nt_k}), {achieved:.0f} GB/s; step phase of the CG "
+    launches = pk["nstep"] // (nt_k - 1) * -(-nt_k // h)
+    step_avg_ms = pk["step_ms"] / max(launches, 1)
+    achieved = bytes_launch / (step_avg_ms * 1e-3) / 1e9
+    traffic = read_traffic("tile2d_f64_square1024", (nw * nr, h), "2dtile")
+    log(f"tile {nw} x {nr} rows, {h} steps per launch")
+    log(f"fp64: {ms_per_step:.3f} ms/step, {value / 1e9:.2f} GLUP/s, {h}-step kernel {1e3 * step_avg_ms:.2f} us "
+        f"({launches} launches at N_T = {nt_k}), {achieved:.0f} GB/s; step phase of the CG "
         f"iteration {phase_gbs:.0f} GB/s")
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic,
-                "kernel": f"multi2d_kernel<double,V={tv},TY={tr},K={fuse},FORCE=0,COMP=0>",
-                "bytes_per_lup": BYTES_PER_MULTI_LAUNCH["f64"] / fuse, "lup_per_launch": fuse * nodes,
-                "bytes_per_launch": BYTES_PER_MULTI_LAUNCH["f64"] * nodes,
+                "kernel": f"tile2d_kernel<NW={nw},R={nr},FORCE=0,TWO=0>, H={h}",
+                "bytes_per_lup": round(BYTES_PER_MULTI_LAUNCH["f64"] / h, 3), "lup_per_launch": h * nodes,
+                "bytes_per_launch": bytes_launch,
                 "avg_launch_us": round(1e3 * step_avg_ms, 3),
-                "launch_timing": f"{pk['nstep'] // fuse} launches, same workload and tiling at N_T = {nt_k}",
+                "launch_timing": f"{launches} launches, same workload at N_T = {nt_k}",
                 # bytes the counters saw moved per launch over the same duration
                 "traffic_GBs": round(traffic / (step_avg_ms * 1e-3) / 1e9, 1) if traffic else None,
                 "step_phase_GBs": round(phase_gbs, 1),
                 # effective fraction: lattice updates per second times the
                 # single-step algorithmic bytes (104 B/LUP), the measure under
-                # which temporal blocking can exceed 1 (the K-step kernel
-                # needs 120/K B/LUP, frac above)
-                "effective_frac_kernel": round(fuse * nodes / (step_avg_ms * 1e-3) * BYTES_PER_LUP[(2, "f64", 1)]
+                # which temporal blocking can exceed 1 (the H-step kernel
+                # needs 120/H B/LUP, frac above)
+                "effective_frac_kernel": round(h * nodes / (step_avg_ms * 1e-3) * BYTES_PER_LUP[(2, "f64", 1)]
                                                / (HBM_PEAK_GBS * 1e9), 4),
                 "effective_frac_end_to_end": round(value * BYTES_PER_LUP[(2, "f64", 1)] / (HBM_PEAK_GBS * 1e9), 4),
-                "note": (f"temporal blocking: {fuse} time steps per launch at 120 B per node and launch "
-                         f"({BYTES_PER_MULTI_LAUNCH['f64'] / fuse:g} B per lattice update); frac prices the kernel "
-                         "at its own bytes, effective_frac_* price lattice updates at the single step's 104 B; "
-                         "the launch is latency- and issue-bound at two waves per SIMD, not bandwidth-bound")}
+                "note": (f"temporal blocking: {h} time steps per launch at 120 B per node and launch "
+                         f"({BYTES_PER_MULTI_LAUNCH['f64'] / h:.3g} B per lattice update), halos of the tiles not "
+                         "counted; frac prices the kernel at its own bytes, effective_frac_* price lattice updates at "
+                         "the single step's 104 B; about half of a launch is its loads and stores, half FP64 issue "
+                         "at two waves per SIMD")}
     ctx.close()
 
     variants = {}
@@ -922,13 +951,13 @@ def main():
     c3 = inputs.layered_cube()
     n3 = unknown_nodes(c3)
     for tag, kw in (("f64", {}), ("f32c", {"prec": elwh.FP32_STEP, "compensated": 1})):
-        for fuse3 in (2, 1):
+        for fuse3 in ((2, 1) if tag != "f64" else (2,)):   # (FP64 marches single steps)
             ctx3 = elwh.context_from_case(c3, fuse=fuse3, **kw)
             nt3 = ctx3.info()["nt"]
             p = kernel_rate(ctx3, 2)
             step_us = 1e3 * p["step_ms"] / max(p["nstep"], 1)      # per time step
             rb, tz = ctx3.get_tile(elwh.FP32_STEP if tag != "f64" else elwh.FP64)
-            two = fuse3 >= 2 and rb >= 2
+            two = tag != "f64" and fuse3 >= 2 and rb >= 2
             # the N_T - 1 steps after the half step: pair launches, and one
             # single step when N_T - 1 is odd
             pairs = (nt3 - 1) // 2 if two else 0
@@ -937,7 +966,7 @@ def main():
             bytes_per_lup = bytes_app / ((nt3 - 1) * n3)
             gbs = bytes_per_lup * n3 / step_us / 1e3
             key = "3d_" + tag + ("" if fuse3 >= 2 else "_single")
-            variants[key] = {"workload": c3.name, "nt": nt3, "tile_rows_planes": [rb, tz],
+            variants[key] = {"workload": c3.name, "nt": nt3, "tile_rows_planes": [rb, tz] if tag != "f64" else None,
                              "steps_per_launch": 2 if two else 1, "step_us": round(step_us, 2),
                              "launches_per_application": pairs + single,
                              "glup_s_kernel": round(n3 / step_us / 1e3, 3),

@@ -496,9 +496,11 @@ elwh_status elwh_autotune(elwh_ctx* ctx, int prec, int reps, double* best_step_u
 /*
  * Ragged batch of independent 2-D problems (sizes, media, omega and N_T may
  * all differ), solved together: each batched step ("tick") advances every
- * unfinished problem by opts->fuse >= 4 ? 4 : 2 steps of its own filter
- * application where that many are left (one step where not, and always
- * for opts->fuse = 1), in one multi-step and one single-step launch over
+ * unfinished problem by several steps of its own filter application in one
+ * launch: FP64 with opts->fuse >= 4 by up to 4 to 10 (one count for the batch,
+ * from its sizes), otherwise by opts->fuse >= 4 ? 4 : 2 where that many are
+ * left and by one step where not (always for opts->fuse = 1), in one
+ * multi-step and one single-step launch over
  * all problems; a problem whose application ends runs its CG update on the
  * device in the same tick and starts its next application at the next one;
  * converged problems drop out.  The CG phase is captured as a hipGraph of several steps and

@@ -1,9 +1,9 @@
 // Ragged batch of 2-D El-WaveHoltz problems (C ABI in include/elwh.h).
 //
 // Every problem keeps its own context (coefficients, state buffers, work
-// vectors, filter weights and N_T).  One "tick" is one batched step launch
-// that advances every active problem by one time step of its own filter
-// application, followed by the device-side CG updates of the problems whose
+// vectors, filter weights and N_T).  One "tick" is one batched step launch (or
+// a multi-step and a single-step one) that advances every active problem by
+// one or more time steps of its own filter application, followed by the device-side CG updates of the problems whose
 // application ended in that tick (Sec. 4.5: alpha = (r,r)_M/(p,A p)_M,
 // x += alpha p, r -= alpha A p, beta, p = r + beta p, all in FP64 with
 // per-problem two-pass reductions).  A problem that converges drops out; the
@@ -566,7 +566,7 @@ elwh_status elwh_batch_create(int nprob, const elwh_grid* grids, const double* c
     b->h_st.assign(nprob, BState{});
     b->info.assign(nprob, elwh_info{});
     // untuned tiles: supported by the single-step and the kb-step batch kernels
-    const Tile t0 = batch_kb(o.fuse) == 4 ? Tile{1, 10} : Tile{2, 8};
+    const Tile t0 = batch_kb(o.fuse) == 4 ? Tile{1, 10} : Tile{2, 8};   // (FP64 at 4: register tiles instead)
     b->tile[0] = t0;
     b->tile[1] = t0;
     b->reg = batch_kb(o.fuse) == 4;   // (fewer steps per tick asked for: the marching kernels)

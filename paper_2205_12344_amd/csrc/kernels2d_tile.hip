@@ -31,8 +31,6 @@
 // The launch that starts an application takes the even-in-time start u^1 = u^0
 // + (a/2)(Ltilde u^0 - f) (with a second field, + dt (1 - g) u1) as its first step.
 #include <algorithm>
-#include <cstdio>
-#include <cstdlib>
 
 #include "step2d_common.h"
 
@@ -372,9 +370,9 @@ void tile_launch(bool force, hipStream_t s, const double* u, const double* uprev
 // 3 us of load latency and coefficients, 0.04 us per tile row for the loads
 // and 2.4 ns per inner node for its stores (two fields: 5 us and 6 ns).  Fitted
 // to, and within 15 % of, launches of 64^2 to 1500^2 nodes.  Measured, against
-// the marching kernels: 64^2 8 x 3 rows x 11 steps 1.18 us per step (3.91), 256^2
-// 8 x 4 x 12 1.47 (4.16), 611 x 373 8 x 4 x 6 2.20 (5.50), 1024^2 8 x 4 x 7 8.71
-// (10.75); two fields: 256^2 8 x 3 x 7 2.49 (7.01), 1024^2 8 x 3 x 6 14.2 (26.4),
+// the marching kernels: 64^2 8 x 3 rows x 11 steps 1.14 us per step (3.91), 256^2
+// 8 x 4 x 12 1.46 (4.16), 611 x 373 8 x 4 x 6 2.20 (5.50), 1024^2 8 x 4 x 7 8.60
+// (10.75); two fields: 256^2 8 x 3 x 7 2.55 (7.01), 1024^2 8 x 3 x 6 14.8 (26.4),
 // where the 8 x 4 tile spills registers (20.8; with the velocity sum in LDS
 // instead 14.3 at 1024^2 and slower below).
 TileShape tile2d_pick(int nx, int nrows, int N, bool two) {
@@ -403,13 +401,6 @@ TileShape tile2d_pick(int nx, int nrows, int N, bool two) {
 TileShape tile2d_shape(const elwh_ctx* c, bool two) {
     // (fewer steps per launch, or a tiling, asked for: the marching kernels)
     if (c->tile64_set || c->opts.fuse < 4) return TileShape();
-#ifdef TILE_PROBE
-    TileShape t;
-    if (const char* e = getenv("TILE")) {
-        sscanf(e, "%d,%d,%d", &t.NW, &t.R, &t.H);
-        return t;
-    }
-#endif
     const int rows = c->mr.hi - c->mr.lo + 1;
     // One field: beyond about 2000^2 nodes the marching kernels are level (2048^2:
     // 2261 against 2364 us, 4096^2: 8.40 against 8.39 ms) and need no tile
