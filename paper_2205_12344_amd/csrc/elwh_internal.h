@@ -295,6 +295,8 @@ void run_filter_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool wi
 void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x0, const double* z1, bool with_force,
                                 bool amode, double s_in, double s_out, double* out0, double* out1);
 struct Args3D;
+// Whether the FP64 step of a mapped 3-D grid (cells, unknown planes) marches (kernels3d_curv.hip).
+bool march3_pays(int nq, int nr, int ns, int np);
 // The FP64 marching step on 3-D Cartesian grids (kernels3d_march.hip), and whether it is taken.
 bool march3d_pays(const elwh_ctx* c);
 void launch_march3d(bool start, bool force, const Args3D& A, hipStream_t s, const double* u, const double* uprev,

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64) void curv3d_kernel(const U* __restrict__ u, con
     }
 }
 
-// ---- FP64, large grids: marching workgroups that share the fluxes ----------------
+// ---- FP64, all but small grids: marching workgroups that share the fluxes ----------------
 //
 // The gather above forms every node's contribution K^ab (D_b U) again at each of
 // the nodes that use it: 1353 instructions and 134 loads per node, 171 us per
@@ -248,9 +248,8 @@ __global__ __launch_bounds__(64) void curv3d_kernel(const U* __restrict__ u, con
 // A workgroup of 8 wavefronts takes 8 rows (r) of 64 nodes (q), of which 6 x 62
 // are its own, and marches along s: q exports go by DPP, r exports through LDS
 // (two buffers, one barrier per plane), s exports stay in registers.  Every
-// array is read once per plane, one plane ahead.  The number of workgroups is
-// kept to one per CU (their registers fill it): the march is split along s only
-// as far as that allows.
+// array is read once per plane, one plane ahead.  A workgroup's registers fill a CU;
+// the march is split along s into the rounds of workgroups that cost least (march3_chunk).
 // On a free s face (trapezoid weight 1/2): dividing the row by the weight leaves
 // the in-plane terms as they are and doubles those along s; D_s is one-sided, and
 // the face's own F^s enters with its own coefficient.
@@ -459,30 +458,44 @@ __global__ __launch_bounds__(64 * M3_NW) void curv3d_march_kernel(const double* 
     if (kb == k1) finish(k1, ld_centre(k1), um, V3d{0.0, 0.0, 0.0});
 }
 
-// The march costs a few planes' latency before its first store, the gather none:
-// 8.6 k nodes 9.3 against 5.3 us per step, 63 k 10.2 against 8.7, 228 k 18.1
-// against 28.6, 1.88 M 95 against 171.
-static bool march3_pays(const ArgsC3& A) {
-    return (int64_t)(A.nq - 1) * (A.nr - 1) * (A.khi - A.klo + 1) >= 80000;
+// Planes per chunk along s, one workgroup per CU at a time: the fewest rounds
+// times planes (a chunk works on two planes more than it owns).  The shell's 140
+// columns of 40 planes in one round use 140 of 256 CUs: 124 us per step; in five
+// chunks (three rounds of 10 planes) 95.
+static int march3_chunk(int nb, int np) {
+    int tz = np;
+    int64_t best = (int64_t)1 << 60;
+    for (int z = 1; z <= np; ++z) {
+        const int64_t cost = ((int64_t)nb * ((np + z - 1) / z) + 255) / 256 * (z + 2);
+        if (cost <= best) {
+            best = cost;
+            tz = z;
+        }
+    }
+    return tz;
+}
+static int march3_columns(int nq, int nr) { return ((nq - 1 + M3_Q - 1) / M3_Q) * ((nr - 1 + M3_R - 1) / M3_R); }
+
+// The march works through its planes in turn (3.0 us and 2.25 us per plane); the
+// gather has every node in flight at once (3.4 us, 4.2 us per 1000 wavefronts of 64
+// nodes along q, and 1 us once a CU has more than eight of them).  Fitted to up to
+// 4000 wavefronts, where they cross; us per step, gather against march: 40^3 9.7 /
+// 11.8, 44^3 10.8 / 12.0, 63 x 63 x 30 11.2 / 12.3, 120 x 36 x 20 9.3 / 10.2, 300 x 3 x
+// 300 15.8 / 17.3; 47^3 13.4 / 12.1, 150 x 45 x 15 13.6 / 12.1, 63 x 63 x 35 14.1 /
+// 12.4, 200 x 200 x 2 16.8 / 10.7, 400 x 120 x 40 171 / 95.
+bool march3_pays(int nq, int nr, int ns, int np) {
+    const int nb = march3_columns(nq, nr), tz = march3_chunk(nb, np);
+    const int64_t rounds = ((int64_t)nb * ((np + tz - 1) / tz) + 255) / 256;
+    const int64_t waves = (int64_t)((nq - 1 + 63) / 64) * (nr - 1) * np;
+    return 3.0 + 2.25 * (double)(rounds * std::min(tz + 2, ns + 1)) <
+           3.4 + 4.2e-3 * (double)waves + (waves > 8 * 256 ? 1.0 : 0.0);
 }
 
 template <int MODE>
 static void launch_march3(bool force, const ArgsC3& A, hipStream_t s, const double* u, const double* uprev,
                           double* unext, const double* xbase, double* acc, const double* ca, const double* cl,
                           const double* cm, const Metric3<double>& G, const double* f) {
-    const int nb = ((A.nq - 1 + M3_Q - 1) / M3_Q) * ((A.nr - 1 + M3_R - 1) / M3_R), np = A.khi - A.klo + 1;
-    // Chunks along s: one workgroup per CU at a time, so the fewest rounds times
-    // planes (a chunk works on two planes more than it owns).  The shell's 140
-    // columns of 40 planes in one round use 140 of 256 CUs: 124 us per step; in
-    // five chunks (three rounds of 10 planes) 95.
-    int tz = np, best = 1 << 30;
-    for (int z = 1; z <= np; ++z) {
-        const int cost = (nb * ((np + z - 1) / z) + 255) / 256 * (z + 2);
-        if (cost <= best) {
-            best = cost;
-            tz = z;
-        }
-    }
+    const int nb = march3_columns(A.nq, A.nr), np = A.khi - A.klo + 1, tz = march3_chunk(nb, np);
     const dim3 grid((unsigned)xcd_grid(nb * ((np + tz - 1) / tz)));
     if (force)
         hipLaunchKernelGGL((curv3d_march_kernel<MODE, true>), grid, dim3(64 * M3_NW), 0, s, u, uprev, unext, xbase, acc,
@@ -544,7 +557,7 @@ void run_filter_curv3d(elwh_ctx* c, const double* x, bool with_force, bool amode
         for (int q = 0; q < 9; ++q) G.g[q] = c->cg[q];
         double *b0 = c->s64[0], *b1 = c->s64[1];
         prof_mark(c, 0);
-        const bool march = march3_pays(A);
+        const bool march = march3_pays(A.nq, A.nr, A.ns, A.khi - A.klo + 1);
         if (march)
             launch_march3<1>(with_force, A, s, x, nullptr, b1, amode ? x : nullptr, acc, c->ca, c->cl, c->cm, G, c->f64);
         else

@@ -239,3 +239,23 @@ def test_marching_kernel_matches_oracle(E, n, bc):
     ref = wh.apply_filter(prob.gather(u0), prob.gather(f))
     assert _rel(prob.gather(ctx.apply_filter(u0, f).cpu().numpy()), ref) <= FP64_TOL
     assert _rel(prob.gather(ctx.apply_A(u0).cpu().numpy()), wh.apply_A(prob.gather(u0))) <= FP64_TOL
+
+
+@pytest.mark.parametrize("n,bc", [
+    ((125, 61, 21), (0, 0, 0, 0, 1, 1)),      # whole tiles of 62 x 6 nodes, 22 planes in chunks of two
+    ((126, 61, 25), (0, 0, 0, 0, 0, 0)),      # one node more than whole tiles along q
+    ((63, 62, 37), (0, 0, 0, 0, 1, 0)),       # along r
+    ((63, 43, 52), (0, 0, 0, 0, 0, 1)),       # whole tiles, thick in s
+])
+def test_marching_kernel_at_the_sizes_it_takes(E, n, bc):
+    """Grids of more than eight wavefronts per CU in the gathering form march
+    along s: filter with forcing and A_h against the oracle to the FP64 bar."""
+    data, op, wh = _setup(n, bc, (1.9, 1.1), 31, omega=9.0)
+    prob = op.prob
+    rng = np.random.default_rng(8)
+    u0, f = (rng.standard_normal(prob.field_shape) * prob.unknown_mask() for _ in range(2))
+    ctx = E.MappedContext3(*data, 9.0, bc=bc)
+    ref = wh.apply_filter(prob.gather(u0), prob.gather(f))
+    _say("march", n, bc, "nt", wh.nt)
+    assert _rel(prob.gather(ctx.apply_filter(u0, f).cpu().numpy()), ref) <= FP64_TOL
+    assert _rel(prob.gather(ctx.apply_A(u0).cpu().numpy()), wh.apply_A(prob.gather(u0))) <= FP64_TOL

@@ -1,0 +1,34 @@
+"""Host-side checks (no GPU) of the rules that choose between FP64 step kernels:
+at sizes where both kernels were timed, the rule takes the faster one.  The
+rules are C++ functions of the library, called by their linker names."""
+
+import ctypes
+
+import pytest
+
+B, I = ctypes.c_bool, ctypes.c_int
+
+
+@pytest.fixture(scope="module")
+def rule():
+    from paper_2205_12344_amd import elwh
+
+    def get(name, *argtypes, restype=B):
+        f = getattr(elwh.lib, name)
+        f.argtypes, f.restype = argtypes, restype
+        return f
+    return get
+
+
+# (cells, us per step of the gather, of the march), free s faces, best of two runs
+@pytest.mark.parametrize("n,gather,march", [
+    ((8, 8, 8), 5.50, 9.24), ((40, 40, 40), 9.68, 11.81), ((44, 44, 44), 10.78, 12.00), ((63, 63, 30), 11.21, 12.30),
+    ((120, 36, 20), 9.29, 10.19), ((300, 3, 300), 15.76, 17.32), ((64, 64, 40), 15.47, 16.31),
+    ((100, 100, 9), 11.58, 12.06), ((20, 20, 100), 10.26, 11.52),
+    ((47, 47, 47), 13.42, 12.09), ((63, 63, 35), 14.13, 12.37), ((150, 45, 15), 13.62, 12.14),
+    ((100, 100, 12), 15.57, 12.89), ((200, 200, 2), 16.83, 10.73), ((3, 100, 100), 46.66, 21.87),
+    ((20, 20, 200), 17.70, 15.85), ((100, 9, 150), 14.85, 14.01), ((399, 119, 39), 171.0, 95.0),
+])
+def test_mapped_3d_march(rule, n, gather, march):
+    pays = rule("_ZN4elwh11march3_paysEiiii", I, I, I, I)
+    assert pays(*n, n[2] + 1) == (march < gather)
