@@ -68,6 +68,11 @@ struct Args2D {
     int final_;
 };
 
+// What a rule on sizes says about an FP64 step: the kernels that a tiling belongs
+// to (elwh_set_tile), or the register tiles or the march instead; near the line
+// between them one is taken unless both are timed.
+enum StepRule { STEP_TILING = 0, STEP_TILING_UNTIMED = 1, STEP_OWN_UNTIMED = 2, STEP_OWN = 3 };
+
 // Register tiles of a 2-D grid (kernels2d_tile.hip): NW wavefronts of R rows of
 // 64 columns, up to H steps per launch (0: the marching kernels are used).
 constexpr int kTileMaxSteps = 12;
@@ -288,6 +293,9 @@ void launch_step3d_k2(int RB, int TZ, bool force, bool comp, hipStream_t s, cons
 // Cartesian context takes (H = 0: none, the marching kernels), and such an
 // application.
 TileShape tile2d_shape(const elwh_ctx* c, bool two);
+// The rule for grids of few rows: one field on a Cartesian grid, or two fields or a
+// mapped grid (coupled: more work per node and single marching steps).
+StepRule strip2d_rule(int nx, int nrows, bool coupled);
 Tile2D tile2d_args(const elwh_ctx* c, const TileShape& t);
 // The two FP64 state buffers that are neither a nor b.
 void other_two(const elwh_ctx* c, const double* a, const double* b, double** o);

@@ -272,12 +272,13 @@ void curv_tile_launch(bool force, hipStream_t s, const double* u, const double* 
 // its steps (8 x 4 rows 1.41, 8 x 5 rows 1.65 us each).  At 801 x 4003: 35.1 us per
 // step (8 x 5 rows; 8 x 4 rows 38.0, workgroups of 4 wavefronts, two per CU, 36.9, 8 x 6
 // rows spill and take 39.1), marching single steps 80.6; 600 x 1000 6.5 against 16.0,
-// 300 x 300 2.2 against 8.8, 40 x 20 1.9 against 8.0: they serve no size any more,
-// only a tiling that was asked for.
+// 300 x 300 2.2 against 8.8, 40 x 20 1.9 against 8.0: they serve wide grids of a few
+// rows (strip2d_rule) and a tiling that was asked for.
 TileShape curv_tile_shape(const elwh_ctx* c) {
     TileShape best;
     if (c->tile64_set) return best;   // a tiling asked for: the marching kernel
     const int nx = c->L.nx, nrows = c->mr.hi - c->mr.lo + 1, N = c->plan.nt * c->opts.periods;
+    if (strip2d_rule(nx, nrows, true) < STEP_OWN_UNTIMED) return best;
     double tbest = 1e300;
     for (int R = 4; R <= 5; ++R) {
         const int rows = 8 * R;

@@ -407,14 +407,32 @@ TileShape tile2d_pick(int nx, int nrows, int N, bool two) {
     return best;
 }
 
+// Few rows and tens of thousands of columns: a tile computes its 16 to 32 rows
+// however few are unknown, and there are several rounds of them, while the
+// marching wavefronts stop at the last row.  Tiles against the marching kernels,
+// us for 60 steps: 25000 x 2 96 / 154, 28000 x 2 179 / 155, 40000 x 4 246 / 218,
+// 100000 x 3 319 / 252; 50000 x 8 294 / 331, 80000 x 8 478 / 432; 80000 x 16 642 /
+// 706, 120000 x 12 836 / 706; 40000 x 32 679 / 738, 50000 x 48 1310 / 1227,
+// 50000 x 64 1663 / 1655.  Two fields 28000 x 3 276 / 283, 40000 x 3 361 / 297, 100000 x
+// 5 847 / 640, 100000 x 8 930 / 1389; mapped 28000 x 3 304 / 324, 40000 x 3 400 / 339,
+// 100000 x 5 936 / 825, 100000 x 8 988 / 1197.
+StepRule strip2d_rule(int nx, int nrows, bool coupled) {
+    if (nx <= 25000 || nrows >= (coupled ? 6 : 64)) return STEP_OWN;
+    const int widest = coupled ? (nrows <= 3 ? 27000 : (nrows == 4 ? 36000 : 70000))
+                               : (nrows <= 4 ? 27000 : (nrows <= 8 ? 60000 : (nrows <= 23 ? 90000 : 45000)));
+    return nx > widest ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
+}
+
 TileShape tile2d_shape(const elwh_ctx* c, bool two) {
     // (fewer steps per launch, or a tiling, asked for: the marching kernels)
     if (c->tile64_set || c->opts.fuse < 4) return TileShape();
     const int rows = c->mr.hi - c->mr.lo + 1;
     // One field: beyond about 2000^2 nodes the marching kernels are level (2048^2:
     // 2261 against 2364 us, 4096^2: 8.40 against 8.39 ms) and need no tile
-    // redundancy.  Two fields: they take one step per launch, 2.2 times slower.
+    // redundancy.  Two fields: they take one step per launch, twice as slow up to
+    // the largest grid tried (4096^2: 29.4 against 13.7 ms for 61 steps).
     if (!two && (int64_t)c->L.nx * rows > (int64_t)2100 * 2100) return TileShape();
+    if (strip2d_rule(c->L.nx, rows, two) < STEP_OWN_UNTIMED) return TileShape();
     return tile2d_pick(c->L.nx, rows, c->plan.nt * c->opts.periods + (two ? 1 : 0), two);
 }
 

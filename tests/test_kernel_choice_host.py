@@ -32,3 +32,24 @@ def rule():
 def test_mapped_3d_march(rule, n, gather, march):
     pays = rule("_ZN4elwh11march3_paysEiiii", I, I, I, I)
     assert pays(*n, n[2] + 1) == (march < gather)
+
+
+# (columns, rows, us of the tiles, of the marching kernels), 60 steps
+@pytest.mark.parametrize("nx,rows,tiles,march", [
+    (25000, 2, 96, 154), (28000, 2, 179, 155), (40000, 4, 246, 218), (100000, 3, 319, 252), (50000, 8, 294, 331),
+    (80000, 8, 478, 432), (100000, 6, 568, 365), (80000, 16, 642, 706), (120000, 12, 836, 706), (65000, 20, 588, 802),
+    (40000, 32, 679, 738), (50000, 48, 1310, 1227), (30000, 100, 1587, 1655), (64, 8000, 379, 488),
+])
+def test_strips(rule, nx, rows, tiles, march):
+    r = rule("_ZN4elwh12strip2d_ruleEiib", I, I, B, restype=I)
+    assert (r(nx, rows, False) >= 2) == (tiles < march)
+
+
+@pytest.mark.parametrize("nx,rows,tiles,march", [
+    (20000, 2, 186, 268), (28000, 4, 295, 347), (40000, 3, 361, 297), (100000, 2, 772, 297), (100000, 5, 847, 640),
+    (40000, 5, 391, 436), (100000, 8, 930, 1389),
+])
+def test_two_field_strips(rule, nx, rows, tiles, march):
+    """Two fields; a mapped grid's kernels cross at the same sizes."""
+    r = rule("_ZN4elwh12strip2d_ruleEiib", I, I, B, restype=I)
+    assert (r(nx, rows, True) >= 2) == (tiles < march)
