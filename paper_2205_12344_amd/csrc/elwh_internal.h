@@ -306,6 +306,7 @@ struct Args3D;
 // Whether the FP64 step of a mapped 3-D grid (cells, unknown planes) marches (kernels3d_curv.hip).
 bool march3_pays(int nq, int nr, int ns, int np);
 // The FP64 marching step on 3-D Cartesian grids (kernels3d_march.hip), and whether it is taken.
+StepRule march3d_rule(int nx, int ny, int np, bool pairs);   // pairs: the tilings take two steps per launch
 bool march3d_pays(const elwh_ctx* c);
 void launch_march3d(bool start, bool force, const Args3D& A, hipStream_t s, const double* u, const double* uprev,
                     double* unext, const double* base, double* acc, const double* ca, const double* cl,

@@ -207,11 +207,13 @@ __global__ __launch_bounds__(64 * NW) void march3d_kernel(const double* __restri
     if (kb == k1) finish(k1, e, um, L - K);
 }
 
+int columns(int nx, int ny) { return ((nx - 1 + 61) / 62) * ((ny - 1 + NW - 3) / (NW - 2)); }
+
 template <bool START>
 void launch(bool force, const Args3D& A, hipStream_t s, const double* u, const double* uprev, double* unext,
                const double* base, double* acc, const double* ca, const double* cl, const double* cm,
                const double* f) {
-    const int nb = ((A.nx - 1 + 61) / 62) * ((A.ny - 1 + NW - 3) / (NW - 2)), np = A.khi - A.klo + 1;
+    const int nb = columns(A.nx, A.ny), np = A.khi - A.klo + 1;
     // Chunks along z: the fewest rounds of workgroups (one per CU: 162 registers leave
     // two wavefronts per SIMD) times planes (a chunk works on two more than it owns).
     int tz = np;
@@ -234,13 +236,39 @@ void launch(bool force, const Args3D& A, hipStream_t s, const double* u, const d
 
 }  // namespace
 
-// It is the faster one at every size tried (us per step, against the tiling that
-// autotuning picks): 16^3 6.4 (11.5), 32^3 6.3 (11.3), 64^3 14.1 (16.7), 128^3 66 (81),
-// 200 x 150 x 100 95 (132), 256^3 545 (608); the two-step kernel, which computes two
-// halo rows per workgroup, is what it replaces except at 128^3.
+// The march is the faster one on grids that are thick every way (us per step,
+// against the tiling that autotuning picks): 16^3 6.4 (11.5), 32^3 6.3 (11.3), 64^3
+// 14.1 (16.7), 128^3 66 (81), 200 x 150 x 100 95 (132), 256^3 545 (608).  It launches
+// every step and works on two planes and two rows more than it owns, so the
+// two-step launches keep the thin grids that caches hold (us for 20 steps, march
+// against tilings):
+//   few planes: 64 x 64 x 1 118 / 74, x 3 126 / 119, x 4 130 / 141; 200 x 200 x 3 189 /
+//   164; 600 x 600 x 2 579 / 546, x 4 879 / 997; 800 x 800 x 1 701 / 649, x 2 957 / 1063
+//   (planes unknown);
+//   few rows: one row 400 x 400 349 / 284, 400 x 200 222 / 243; two rows 400 x 400 361 /
+//   335, 400 x 300 299 / 326, 62 x 2500 327 / 503;
+//   one round of workgroups that cannot be split further (129 to 256 columns):
+//   200 x 200 x 5 251 / 234, x 9 363 / 368; 240 x 380 x 8 425 / 396; 490 x 180 x 8 418 /
+//   469.
+// With fuse = 1 the tilings step singly too and keep one plane (64 x 64 118 / 90) and
+// one row (400 x 400 349 / 322; two rows 361 / 369, two planes of 200 x 200 159 / 160).
+StepRule march3d_rule(int nx, int ny, int np, bool pairs) {
+    const int64_t nodes = (int64_t)(nx - 1) * (ny - 1) * np;
+    if (nodes > 1500000 && ny > 3) return STEP_OWN;
+    if (np <= (pairs ? 3 : 1)) return nodes <= 1000000 ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
+    if (ny <= (pairs ? 3 : 2)) {
+        if (nodes <= 60000) return STEP_OWN;
+        return nx > 200 && nodes > (ny == 2 ? 100000 : 300000) ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
+    }
+    const int nb = columns(nx, ny);
+    if (!pairs || np > 16 || nb <= 64) return STEP_OWN;
+    return np <= 8 && nb > 128 && nb <= 256 ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
+}
+
 bool march3d_pays(const elwh_ctx* c) {
     // (a tiling asked for; places in a plane are 32-bit byte offsets)
-    return !c->tile64_set && c->L.P * (c->L.ny + 1) < ((int64_t)1 << 29);
+    if (c->tile64_set || c->L.P * (c->L.ny + 1) >= ((int64_t)1 << 29)) return false;
+    return march3d_rule(c->L.nx, c->L.ny, c->mr.hi - c->mr.lo + 1, c->opts.fuse >= 2) >= STEP_OWN_UNTIMED;
 }
 
 void launch_march3d(bool start, bool force, const Args3D& A, hipStream_t s, const double* u, const double* uprev,

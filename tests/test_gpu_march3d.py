@@ -72,3 +72,21 @@ def test_many_rounds_match_tilings(E):
     b.set_tile(E.FP64, 4, 8)
     for p, q in ((a.apply_filter(x, f), b.apply_filter(x, f)), (a.apply_A(x), b.apply_A(x))):
         assert float((p - q).norm() / q.norm()) <= TOL
+
+
+@pytest.mark.parametrize("n,lo,hi", [((1300, 1290, 2), 0, 0), ((1001, 1555, 2), 0, 1), ((1250, 1210, 3), 1, 0),
+                                     ((700, 4, 1100), 1, 1)])
+def test_few_planes_or_rows_of_large_grids_match_tilings(E, n, lo, hi):
+    """One to four planes, or three rows, are marched through where they are large."""
+    import torch
+    bc = (0, 0, 0, 0, lo, hi)
+    shape = tuple(k + 1 for k in n[::-1])
+    rho, lam, mu = _media(shape, 6)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x, f = (torch.randn((3,) + shape, generator=g, device="cuda", dtype=torch.float64) for _ in range(2))
+    kw = dict(length=tuple(k / 100 for k in n), nt=12, autotune=0)
+    a = E.Context(3, n, rho, lam, mu, 50.0, bc, **kw)
+    b = E.Context(3, n, rho, lam, mu, 50.0, bc, **kw)
+    b.set_tile(E.FP64, 4, 8)
+    for p, q in ((a.apply_filter(x, f), b.apply_filter(x, f)), (a.apply_A(x), b.apply_A(x))):
+        assert float((p - q).norm() / q.norm()) <= TOL

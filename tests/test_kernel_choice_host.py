@@ -53,3 +53,27 @@ def test_two_field_strips(rule, nx, rows, tiles, march):
     """Two fields; a mapped grid's kernels cross at the same sizes."""
     r = rule("_ZN4elwh12strip2d_ruleEiib", I, I, B, restype=I)
     assert (r(nx, rows, True) >= 2) == (tiles < march)
+
+
+# (cells along x and y, unknown planes, us of the march, of the tilings), 20 steps
+@pytest.mark.parametrize("nx,ny,np,march,tiling", [
+    (2, 2, 1, 103, 62), (64, 64, 1, 118, 74), (200, 200, 2, 158, 131), (64, 64, 3, 126, 119), (200, 200, 3, 189, 164),
+    (600, 600, 2, 579, 546), (800, 800, 1, 701, 649), (200, 200, 5, 251, 234), (240, 380, 8, 425, 396),
+    (400, 2, 399, 349, 284), (400, 3, 399, 361, 335), (1000, 2, 999, 1447, 894),
+    (64, 64, 4, 130, 141), (20, 20, 19, 128, 230), (600, 600, 4, 879, 997), (800, 800, 2, 957, 1063),
+    (200, 200, 9, 363, 368), (250, 250, 13, 509, 563), (400, 2, 199, 222, 243), (62, 3, 2499, 327, 503),
+    (600, 4, 599, 645, 787), (128, 128, 127, 1423, 1675), (300, 300, 25, 1159, 1444),
+])
+def test_march3d(rule, nx, ny, np, march, tiling):
+    r = rule("_ZN4elwh12march3d_ruleEiiib", I, I, I, B, restype=I)
+    assert (r(nx, ny, np, True) >= 2) == (march < tiling)
+
+
+@pytest.mark.parametrize("nx,ny,np,march,tiling", [
+    (64, 64, 1, 118, 90), (200, 200, 1, 125, 116), (800, 800, 1, 703, 649), (400, 2, 399, 349, 322),
+    (64, 64, 3, 126, 136), (300, 300, 8, 426, 475), (400, 3, 399, 361, 369), (20, 3, 1999, 265, 291),
+    (64, 64, 63, 291, 364),
+])
+def test_march3d_against_single_step_tilings(rule, nx, ny, np, march, tiling):
+    r = rule("_ZN4elwh12march3d_ruleEiiib", I, I, I, B, restype=I)
+    assert (r(nx, ny, np, False) >= 2) == (march < tiling)
