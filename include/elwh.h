@@ -103,16 +103,19 @@ typedef struct {
                           FP64 residual replacements (default 1e-2) */
     int max_outer;     /* FP32 path: maximum residual replacements (default 50) */
     void* stream;      /* hipStream_t the context works on; NULL = the null stream */
-    int autotune;      /* 1 (default): pick the step-kernel tiling by timing at create */
+    int autotune;      /* 1 (default): pick the step-kernel tiling by timing at create,
+                          where the grid's size does not decide (elwh_autotune) */
     int fuse;          /* time steps per step-kernel launch: 2-D Cartesian 1 to 4,
                           3-D Cartesian 1 or 2 (larger values act as 2, and
                           the tiling may still choose single steps, which
-                          FP64 takes where no tiling was asked for); default 4;
+                          FP64 takes on all but thin grids where no tiling
+                          was asked for); default 4;
                           mapped grids ignore it.  In FP64 on 2-D
                           Cartesian grids 4 also lets the library take more
                           (register tiles of up to 12 steps, up to about
-                          2000^2 nodes; the two-field step at every size)
-                          unless elwh_set_tile asked for a tiling; the
+                          2000^2 nodes; the two-field step at every size;
+                          neither on grids of a few rows and more than 25 000
+                          columns) unless elwh_set_tile asked for a tiling; the
                           two-field step is single for 1 to 3.  The batch
                           takes four-step ticks for 4, two-step for 2 and 3 */
     int scale_x0;      /* CG paths: 1 = replace a given x0 by alpha x0 with
@@ -476,17 +479,26 @@ elwh_status elwh_profile_read(elwh_ctx* ctx, double* step_ms, int* nstep, double
  * (1, 2, 4, 8) x (4, 8, 16, 32) for single-step launches (opts.fuse = 1),
  * (2, 4, 6) x (8, 16, 32, 64) for two-step launches (fuse >= 2; the workgroup
  * adds two halo rows), where vec = 1 with rows 4 to 32 makes every step a
- * single-step launch (the FP64 choice on large cubes).  The tiling changes
- * speed only, never results.  It is that of the kernels which FP32 stepping
- * and, on 2-D Cartesian grids, opts.fuse < 4 and large grids use; setting an
- * FP64 tiling makes FP64 stepping use them on 2-D grids and 3-D Cartesian ones.
- * elwh_autotune times every supported tiling on reps operator applications
- * (HIP events), in three round-robin passes, and keeps the tiling with the
- * fastest pass (contexts with impedance faces time the two-field step);
- * results are cached per process by
+ * single-step launch (the FP64 choice on large cubes).  Tilings
+ * agree with each other to rounding.  They are those of the kernels which FP32
+ * stepping uses, and FP64 stepping where opts.fuse < 4 on 2-D Cartesian grids,
+ * on very large or thin grids, or for an FP64 tiling that elwh_set_tile asked for;
+ * elsewhere FP64 steps take register tiles (2-D) or a march (3-D) that have no
+ * tiling and agree with the tiled kernels to rounding.  elwh_get_tile returns
+ * the tiling in either case; setting it again selects the tiled kernel.  A 3-D
+ * mapped grid has one tiling, which selects nothing.
+ * elwh_autotune times every supported tiling, and for FP64 the register tiles
+ * or the march where the context may take them, on reps operator applications
+ * (HIP events), in three round-robin passes, and keeps what had the
+ * fastest pass (contexts with impedance faces time the two-field step),
+ * also over an earlier elwh_set_tile; best_step_us is that pass's time per step.
+ * Choices are cached per process by
  * (dim, precision, accumulator, grid size) and, when the environment
  * variable ELWH_TUNE_CACHE names a file, in that file as JSON lines keyed by
- * (arch, dim, precision, accumulator, grid size).  Synchronous.
+ * (arch, dim, precision, accumulator, grid size); a choice found there is taken and
+ * best_step_us is -1.  opts.autotune = 1 does the same at create, but times
+ * nothing in FP64 where the grid's size decides for the register tiles or the march
+ * (a choice made by elwh_autotune before is kept).  Synchronous.
  * Errors: ELWH_ERR_ARG (unsupported tiling), ELWH_ERR_HIP.
  */
 elwh_status elwh_set_tile(elwh_ctx* ctx, int prec, int vec, int rows);

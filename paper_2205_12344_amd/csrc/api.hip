@@ -660,6 +660,7 @@ elwh_status ctx_solve_fallback(elwh_ctx* c, int method, double tol, int maxit, i
 }  // namespace elwh
 
 namespace {
+bool adopt_own64(elwh_ctx* c);
 // Create a context; xc/yc non-null: a mapped 2-D grid with these node
 // coordinates (host copies are taken here, like the materials).
 elwh_status create_impl(const elwh_grid* grid_in, const double* xc, const double* yc, const double* zc, const double* rho,
@@ -954,7 +955,8 @@ elwh_status create_impl(const elwh_grid* grid_in, const double* xc, const double
         c->tile32 = Tile{1, 16};
     }
     if (o.autotune) {
-        if ((st = elwh_autotune(c, ELWH_FP64, 2, nullptr)) != ELWH_OK) return fail(st);
+        // (nothing is timed where the sizes decide for register tiles or the march)
+        if (!adopt_own64(c) && (st = elwh_autotune(c, ELWH_FP64, 2, nullptr)) != ELWH_OK) return fail(st);
         if (o.prec == ELWH_FP32_STEP && (st = elwh_autotune(c, ELWH_FP32_STEP, 2, nullptr)) != ELWH_OK)
             return fail(st);
     }
@@ -1606,7 +1608,9 @@ namespace {
 void run_filter_twofield(elwh_ctx* c, const double* x0, const double* z1, bool with_force, bool amode, double s_in,
                          double s_out, double* out0, double* out1);
 // dim, prec, variant (bit 0: compensated accumulator, bits 1-2: steps per
-// 2-D launch minus one, bit 3: mapped grid, bit 4: two-field step), nx, ny, nz
+// 2-D launch minus one, bit 3: mapped grid, bit 4: two-field step, bit 5: the
+// register tiles or the march are among the candidates), nx, ny, nz; the choice
+// {0, 0} stands for those
 using TuneKey = std::tuple<int, int, int, int, int, int>;
 std::mutex g_tune_mu;
 std::map<TuneKey, Tile> g_tune;
@@ -1655,6 +1659,60 @@ void file_store(const TuneKey& k, const std::string& arch, const Tile& t, double
                  std::get<5>(k), t.V, t.TY, us);
     std::fclose(fp);
 }
+
+// The FP64 rule of the context's own operator (a mapped 3-D grid has one tiling, and
+// its march is not a matter of tilings).
+StepRule step_rule(const elwh_ctx* c) {
+    if (c->mapped) return c->L.dim == 3 ? STEP_TILING : strip2d_rule(c->L.nx, c->mr.hi - c->mr.lo + 1, true);
+    return c->L.dim == 3 ? march3d_rule(c) : tile2d_rule(c, has_impedance(c));
+}
+
+TuneKey tune_key(const elwh_ctx* c, bool fp32) {
+    // a context with impedance faces runs the two-field step kernel
+    const bool twofield = !fp32 && has_impedance(c);
+    const int steps = !c->mapped && !twofield ? (c->L.dim == 2 ? c->opts.fuse : std::min(c->opts.fuse, 2)) : 1;
+    const int variant = (fp32 && c->opts.compensated ? 1 : 0) | ((steps - 1) << 1) | (c->mapped ? 8 : 0) |
+                        (twofield ? 16 : 0) | (!fp32 && step_rule(c) != STEP_TILING ? 32 : 0);
+    return TuneKey(c->L.dim, fp32 ? 1 : 0, variant, c->L.nx, c->L.ny, c->L.nz);
+}
+
+// The choice of this process, or of the file, for a key.
+bool cached_choice(const TuneKey& key, Tile* t) {
+    {
+        std::lock_guard<std::mutex> g(g_tune_mu);
+        auto it = g_tune.find(key);
+        if (it != g_tune.end()) {
+            *t = it->second;
+            return true;
+        }
+    }
+    if (!std::getenv("ELWH_TUNE_CACHE") || !file_lookup(key, device_arch(), t)) return false;
+    std::lock_guard<std::mutex> g(g_tune_mu);
+    g_tune[key] = *t;
+    return true;
+}
+
+void take_choice(elwh_ctx* c, bool fp32, const Tile& t) {
+    if (t.V > 0) (fp32 ? c->tile32 : c->tile64) = t;
+    if (fp32) return;
+    c->tile64_set = false;
+    if (step_rule(c) != STEP_TILING) c->own64 = t.V > 0 ? 0 : 1;
+}
+
+// At create: where the sizes alone decide for register tiles or the march, take
+// them, or what elwh_autotune found for such a context, and time nothing.
+bool adopt_own64(elwh_ctx* c) {
+    if (step_rule(c) != STEP_OWN) return false;
+    const TuneKey key = tune_key(c, false);
+    Tile t;
+    if (!cached_choice(key, &t)) {
+        t = Tile{0, 0};
+        std::lock_guard<std::mutex> g(g_tune_mu);
+        g_tune[key] = t;
+    }
+    take_choice(c, false, t);
+    return true;
+}
 }  // namespace
 
 extern "C" {
@@ -1666,28 +1724,12 @@ elwh_status elwh_autotune(elwh_ctx* c, int prec, int reps, double* best_step_us)
         c->err = "FP32 tiling needs an FP32 context";
         return ELWH_ERR_ARG;
     }
-    // a context with impedance faces runs the two-field step kernel: tune that
-    const bool twofield = !fp32 && (c->imp[0] || c->imp[1] || c->ximp[0] || c->ximp[1]);
+    const bool twofield = !fp32 && has_impedance(c);
     const int steps = !c->mapped && !twofield ? (c->L.dim == 2 ? c->opts.fuse : std::min(c->opts.fuse, 2)) : 1;
-    const int comp = (fp32 && c->opts.compensated ? 1 : 0) | ((steps - 1) << 1) | (c->mapped ? 8 : 0) |
-                     (twofield ? 16 : 0);
-    const TuneKey key(c->L.dim, fp32 ? 1 : 0, comp, c->L.nx, c->L.ny, c->L.nz);
-    Tile& dst = fp32 ? c->tile32 : c->tile64;
-    {
-        std::lock_guard<std::mutex> g(g_tune_mu);
-        auto it = g_tune.find(key);
-        if (it != g_tune.end()) {
-            dst = it->second;
-            if (best_step_us) *best_step_us = -1.0;
-            return ELWH_OK;
-        }
-    }
-    const std::string arch = device_arch();
-    Tile ft;
-    if (file_lookup(key, arch, &ft)) {
-        dst = ft;
-        std::lock_guard<std::mutex> g(g_tune_mu);
-        g_tune[key] = ft;
+    const TuneKey key = tune_key(c, fp32);
+    Tile cached;
+    if (cached_choice(key, &cached)) {
+        take_choice(c, fp32, cached);
         if (best_step_us) *best_step_us = -1.0;
         return ELWH_OK;
     }
@@ -1715,18 +1757,22 @@ elwh_status elwh_autotune(elwh_ctx* c, int prec, int reps, double* best_step_us)
         for (int RB : {1, 2, 4})
             for (int TZ : {8, 16, 32}) cands.push_back(Tile{RB, TZ});
     }
+    if (!fp32 && step_rule(c) != STEP_TILING) cands.push_back(Tile{0, 0});   // register tiles or the march
     double* in = c->vec[VT];
     double* out = c->vec[VD];
-    HIPCK(hipMemsetAsync(in, 0, c->L.field_elems() * sizeof(double), c->stream));
+    // (zeros draw less power and favour the kernels with more arithmetic: 300 x 300 x 12
+    // march 494 us on zeros, 543 on a field, tiling 515 and 521)
+    launch_noise(c, in, c->stream);
     hipEvent_t e0, e1;
     HIPCK(hipEventCreate(&e0));
     HIPCK(hipEventCreate(&e1));
     const bool prof = c->prof_on, tile_set = c->tile64_set;
+    const int own = c->own64;
+    const Tile before = fp32 ? c->tile32 : c->tile64;
     c->prof_on = false;
-    c->tile64_set = true;   // the tilings being timed are those of the marching kernels
     const int napply = c->napply;
     double best = 1e300;
-    Tile bt = dst;
+    Tile bt = before;
     // three round-robin passes over the candidates, each candidate's fastest
     // pass counts: a single pass can be skewed by clock ramps and warm-up
     std::vector<double> fastest(cands.size(), 1e300);
@@ -1739,7 +1785,7 @@ elwh_status elwh_autotune(elwh_ctx* c, int prec, int reps, double* best_step_us)
     bool ok = true;
     for (int pass = 0; pass < 3 && ok; ++pass) {
         for (size_t ci = 0; ci < cands.size(); ++ci) {
-            dst = cands[ci];
+            take_choice(c, fp32, cands[ci]);
             if (pass == 0) once();   // warm-up (first launch of this instantiation)
             (void)hipEventRecord(e0, c->stream);
             for (int r = 0; r < reps; ++r) once();
@@ -1761,15 +1807,21 @@ elwh_status elwh_autotune(elwh_ctx* c, int prec, int reps, double* best_step_us)
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     c->prof_on = prof;
-    c->tile64_set = tile_set;
     c->napply = napply;
-    dst = bt;
+    (fp32 ? c->tile32 : c->tile64) = before;   // (reported where register tiles or the march are taken)
+    if (!ok) {
+        c->tile64_set = tile_set;
+        c->own64 = own;
+        c->err = "timing the step kernels failed";
+        return ELWH_ERR_HIP;
+    }
+    take_choice(c, fp32, bt);
     HIPCK(hipGetLastError());
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
         g_tune[key] = bt;
     }
-    file_store(key, arch, bt, best);
+    file_store(key, device_arch(), bt, best);
     if (best_step_us) *best_step_us = best;
     return ELWH_OK;
 }

@@ -95,6 +95,15 @@ PackArgs pack_args(const Layout& L, const int bc[6], int mask) {
     return a;
 }
 
+// Values in [-1, 1) from a hash of their index at the unknown nodes, 0 elsewhere.
+__global__ void noise_kernel(double* __restrict__ x, const double* __restrict__ mw, int64_t CS, int64_t n) {
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        unsigned long long h = (unsigned long long)(e + 1) * 0x9e3779b97f4a7c15ull;
+        h = (h ^ (h >> 29)) * 0xbf58476d1ce4e5b9ull;
+        x[e] = mw[e % CS] > 0.0 ? (double)(long long)(h ^ (h >> 32)) * 0x1p-63 : 0.0;
+    }
+}
+
 unsigned grid_for(int64_t n, int bs = 256) {
     int64_t g = (n + bs - 1) / bs;
     return (unsigned)std::min<int64_t>(std::max<int64_t>(g, 1), 65536);
@@ -377,6 +386,11 @@ void launch_multiaxpy2(const elwh_ctx* c, const double* const* V, int k, const d
         hipLaunchKernelGGL(multiaxpy_kernel<2>, dim3(grid_for(n, RB)), dim3(RB), 0, s, V, k, h, wa, wb, n);
     else
         hipLaunchKernelGGL(multiaxpy_kernel<1>, dim3(grid_for(n, RB)), dim3(RB), 0, s, V, k, h, wa, wa, n);
+}
+
+void launch_noise(const elwh_ctx* c, double* x, hipStream_t s) {
+    const int64_t n = c->L.field_elems();
+    hipLaunchKernelGGL(noise_kernel, dim3(grid_for(n)), dim3(256), 0, s, x, c->mw, c->L.CS, n);
 }
 
 void launch_copy(const elwh_ctx* c, const double* x, double* y, hipStream_t s) {

@@ -200,7 +200,8 @@ struct elwh_ctx {
 
     // tiling of the fused step kernels (set by elwh_set_tile / elwh_autotune)
     elwh::Tile tile64, tile32;
-    bool tile64_set = false;           // the FP64 tiling was asked for: no register tiles
+    bool tile64_set = false;           // the FP64 tiling was asked for: no register tiles, no march
+    int own64 = -1;                    // of the context's operator: register tiles or the march timed faster (1), a tiling (0), not timed (-1)
 
     // kernel profiling: three events per filter application (start, after the
     // half step, after the last step) on the context's stream
@@ -293,6 +294,14 @@ void launch_step3d_k2(int RB, int TZ, bool force, bool comp, hipStream_t s, cons
 // Cartesian context takes (H = 0: none, the marching kernels), and such an
 // application.
 TileShape tile2d_shape(const elwh_ctx* c, bool two);
+StepRule tile2d_rule(const elwh_ctx* c, bool two);
+// Whether FP64 steps take the register tiles or the march, by what was asked for,
+// timed (main: the context's own operator, which the timing is of), or the rule.
+inline bool own_steps(const elwh_ctx* c, StepRule rule, bool main) {
+    if (c->tile64_set || rule == STEP_TILING) return false;
+    return main && c->own64 >= 0 ? c->own64 == 1 : rule >= STEP_OWN_UNTIMED;
+}
+inline bool has_impedance(const elwh_ctx* c) { return c->imp[0] || c->imp[1] || c->ximp[0] || c->ximp[1]; }
 // The rule for grids of few rows: one field on a Cartesian grid, or two fields or a
 // mapped grid (coupled: more work per node and single marching steps).
 StepRule strip2d_rule(int nx, int nrows, bool coupled);
@@ -307,7 +316,7 @@ struct Args3D;
 bool march3_pays(int nq, int nr, int ns, int np);
 // The FP64 marching step on 3-D Cartesian grids (kernels3d_march.hip), and whether it is taken.
 StepRule march3d_rule(int nx, int ny, int np, bool pairs);   // pairs: the tilings take two steps per launch
-bool march3d_pays(const elwh_ctx* c);
+StepRule march3d_rule(const elwh_ctx* c);
 void launch_march3d(bool start, bool force, const Args3D& A, hipStream_t s, const double* u, const double* uprev,
                     double* unext, const double* base, double* acc, const double* ca, const double* cl,
                     const double* cm, const double* f);
@@ -370,6 +379,7 @@ void launch_cg_update_xr(const elwh_ctx* c, double* x, double* r, const double* 
                          hipStream_t s);
 void launch_cg_update_p(const elwh_ctx* c, double* p, const double* r, hipStream_t s);
 void launch_axpby(const elwh_ctx* c, double a, const double* x, double b, double* y, hipStream_t s);
+void launch_noise(const elwh_ctx* c, double* x, hipStream_t s);   // a field for timing
 void launch_copy(const elwh_ctx* c, const double* x, double* y, hipStream_t s);
 // GMRES orthogonalisation with device coefficients (blas.hip).  Two-field
 // (wb != null): V is a device array of 2k field pointers, vector i = (V[2i],

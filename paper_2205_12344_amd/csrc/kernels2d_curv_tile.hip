@@ -276,9 +276,8 @@ void curv_tile_launch(bool force, hipStream_t s, const double* u, const double* 
 // rows (strip2d_rule) and a tiling that was asked for.
 TileShape curv_tile_shape(const elwh_ctx* c) {
     TileShape best;
-    if (c->tile64_set) return best;   // a tiling asked for: the marching kernel
     const int nx = c->L.nx, nrows = c->mr.hi - c->mr.lo + 1, N = c->plan.nt * c->opts.periods;
-    if (strip2d_rule(nx, nrows, true) < STEP_OWN_UNTIMED) return best;
+    if (!own_steps(c, strip2d_rule(nx, nrows, true), true)) return best;   // the marching kernel
     double tbest = 1e300;
     for (int R = 4; R <= 5; ++R) {
         const int rows = 8 * R;

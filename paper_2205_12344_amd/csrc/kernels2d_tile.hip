@@ -423,17 +423,20 @@ StepRule strip2d_rule(int nx, int nrows, bool coupled) {
     return nx > widest ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
 }
 
-TileShape tile2d_shape(const elwh_ctx* c, bool two) {
-    // (fewer steps per launch, or a tiling, asked for: the marching kernels)
-    if (c->tile64_set || c->opts.fuse < 4) return TileShape();
+StepRule tile2d_rule(const elwh_ctx* c, bool two) {
+    if (c->opts.fuse < 4) return STEP_TILING;   // (fewer steps per launch asked for)
     const int rows = c->mr.hi - c->mr.lo + 1;
     // One field: beyond about 2000^2 nodes the marching kernels are level (2048^2:
     // 2261 against 2364 us, 4096^2: 8.40 against 8.39 ms) and need no tile
     // redundancy.  Two fields: they take one step per launch, twice as slow up to
     // the largest grid tried (4096^2: 29.4 against 13.7 ms for 61 steps).
-    if (!two && (int64_t)c->L.nx * rows > (int64_t)2100 * 2100) return TileShape();
-    if (strip2d_rule(c->L.nx, rows, two) < STEP_OWN_UNTIMED) return TileShape();
-    return tile2d_pick(c->L.nx, rows, c->plan.nt * c->opts.periods + (two ? 1 : 0), two);
+    if (!two && (int64_t)c->L.nx * rows > (int64_t)2100 * 2100) return STEP_TILING;
+    return strip2d_rule(c->L.nx, rows, two);
+}
+
+TileShape tile2d_shape(const elwh_ctx* c, bool two) {
+    if (!own_steps(c, tile2d_rule(c, two), two == has_impedance(c))) return TileShape();
+    return tile2d_pick(c->L.nx, c->mr.hi - c->mr.lo + 1, c->plan.nt * c->opts.periods + (two ? 1 : 0), two);
 }
 
 Tile2D tile2d_args(const elwh_ctx* c, const TileShape& t) {

@@ -337,7 +337,7 @@ void run_filter_3d(elwh_ctx* c, const double* x, bool with_force, bool amode, bo
     A.w0 = sgn * c->w[0];
     A.w = sgn * c->w[1];
     A.fc = c->cosn[0];
-    if (!fp32 && march3d_pays(c)) {
+    if (!fp32 && own_steps(c, march3d_rule(c), true)) {
         prof_mark(c, 0);
         launch_march3d(true, with_force, A, s, x, nullptr, c->s64[1], amode ? x : nullptr, acc, c->ca, c->cl, c->cm,
                        c->f64);

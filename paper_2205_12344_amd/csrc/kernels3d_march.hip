@@ -255,7 +255,8 @@ void launch(bool force, const Args3D& A, hipStream_t s, const double* u, const d
 StepRule march3d_rule(int nx, int ny, int np, bool pairs) {
     const int64_t nodes = (int64_t)(nx - 1) * (ny - 1) * np;
     if (nodes > 1500000 && ny > 3) return STEP_OWN;
-    if (np <= (pairs ? 3 : 1)) return nodes <= 1000000 ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
+    if (np <= (pairs ? 3 : 1))
+        return nodes <= 500000 ? STEP_TILING : (nodes <= 1000000 ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED);
     if (ny <= (pairs ? 3 : 2)) {
         if (nodes <= 60000) return STEP_OWN;
         return nx > 200 && nodes > (ny == 2 ? 100000 : 300000) ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
@@ -265,10 +266,10 @@ StepRule march3d_rule(int nx, int ny, int np, bool pairs) {
     return np <= 8 && nb > 128 && nb <= 256 ? STEP_TILING_UNTIMED : STEP_OWN_UNTIMED;
 }
 
-bool march3d_pays(const elwh_ctx* c) {
-    // (a tiling asked for; places in a plane are 32-bit byte offsets)
-    if (c->tile64_set || c->L.P * (c->L.ny + 1) >= ((int64_t)1 << 29)) return false;
-    return march3d_rule(c->L.nx, c->L.ny, c->mr.hi - c->mr.lo + 1, c->opts.fuse >= 2) >= STEP_OWN_UNTIMED;
+StepRule march3d_rule(const elwh_ctx* c) {
+    // (places in a plane are 32-bit byte offsets)
+    if (c->L.P * (c->L.ny + 1) >= ((int64_t)1 << 29)) return STEP_TILING;
+    return march3d_rule(c->L.nx, c->L.ny, c->mr.hi - c->mr.lo + 1, c->opts.fuse >= 2);
 }
 
 void launch_march3d(bool start, bool force, const Args3D& A, hipStream_t s, const double* u, const double* uprev,
