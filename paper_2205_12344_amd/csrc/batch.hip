@@ -119,7 +119,7 @@ elwh_status set_phase(elwh_batch* b, bool fp32, int isrc, int iout, int ix, int 
         q.nblk2 = q.nbx2 * ((nrows + t.TY - 1) / t.TY);
         if (b->H > 0) q.nblk2 = batch_reg_tiles(q.A.nx, nrows, b->H, &q.nbx2);
         q.off2 = off2;
-        off2 += b->H > 0 ? (q.nblk2 + 7) / 8 : q.nblk2;   // (register tiles are dealt per XCD)
+        off2 += q.nblk2;
         q.nsteps = c->plan.nt * c->opts.periods;
         q.w = b->d_w[p];
         q.cosn = b->d_cos[p];
@@ -185,7 +185,7 @@ elwh_status retile_active(elwh_batch* b, int* nblocks, int* nblocks2) {
         off += q.nblk;
         q.off2 = off2;
         q.nblk2 = live ? b->full_blk2[p] : 0;
-        off2 += b->H > 0 ? (q.nblk2 + 7) / 8 : q.nblk2;
+        off2 += q.nblk2;
     }
     *nblocks = off;
     *nblocks2 = off2;

@@ -402,13 +402,13 @@ inline int batch_kb(int fuse) { return fuse >= 4 ? 4 : (fuse >= 2 ? 2 : 0); }
 bool batch_tile_valid(bool fp32, int V, int TY, int kb);
 // Register-tile ticks of an FP64 batch (kernels2d_tile.hip): tiles of a problem
 // (and tiles along x), the steps per tick for a set of problems, and the tick
-// (neighths: the sum over problems of an eighth of their tiles, rounded up).
+// (ntiles: the sum over problems of their tiles).
 struct BatchSize {
     int nx, nrows, nsteps;
 };
 int batch_reg_tiles(int nx, int nrows, int H, int* ntx);
 int batch_reg_steps(const std::vector<BatchSize>& probs);
-void launch_batch_tiles(bool force, int neighths, int H, hipStream_t s, const BProb2D* pr, const BState* st, int np,
+void launch_batch_tiles(bool force, int ntiles, int H, hipStream_t s, const BProb2D* pr, const BState* st, int np,
                         double sgn, int amode);
 int batch_cols(int V);
 Args2D make_args2d(const elwh_ctx* c);

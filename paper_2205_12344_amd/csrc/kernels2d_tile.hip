@@ -541,16 +541,20 @@ template <bool FORCE>
 __global__ __launch_bounds__(64 * BNW) void batch_tile2d_kernel(const BProb2D* __restrict__ pr,
                                                                const BState* __restrict__ st, int np, int H, double sgn,
                                                                int amode) {
-    // XCD x takes one eighth of every problem's tiles (off2 counts eighths), so
-    // the XCDs stay even when some problems have finished: dealt in one band over
-    // all problems, the tiles of the problems left fell to one or two XCDs
-    // (batch of 16 problems of 256^2 to 1024^2: 237 ms for three iterations).
-    const int x = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-    const int p = batch_problem_of(pr, np, slot, true);
+    const int p = batch_problem_of(pr, np, (int)blockIdx.x, true);
     const BProb2D& q = pr[p];
     if (!st[p].active) return;
-    const int local = x * ((q.nblk2 + kXcds - 1) / kXcds) + slot - q.off2, n = st[p].end ? 0 : st[p].n;
-    if (slot - q.off2 >= (q.nblk2 + kXcds - 1) / kXcds || local >= q.nblk2) return;
+    // Workgroup b runs on XCD b mod 8.  The workgroups of a problem that share an
+    // XCD take one contiguous eighth of its tiles, so the XCDs stay even when some
+    // problems have finished: dealt in one band over all problems, the tiles of
+    // the problems left fell to one or two XCDs (batch of 16 problems of 256^2 to
+    // 1024^2: 237 ms for three iterations).  Every workgroup has a tile: a whole
+    // number of eights per problem left 1000 problems of 30^2 nodes with seven empty
+    // workgroups of eight (four iterations 28.1 ms, now 23.4; three of 48 problems of
+    // 256^2 38.5, now 36.2).
+    const int slot = (int)blockIdx.x - q.off2, share = q.nblk2 / kXcds, more = q.nblk2 % kXcds, e = slot % kXcds;
+    const int local = e * share + min(e, more) + slot / kXcds, n = st[p].end ? 0 : st[p].n;
+    if (slot >= q.nblk2) return;
     Tile2D A;
     A.nx = q.A.nx;
     A.ny = q.A.ny;
@@ -614,10 +618,10 @@ int batch_reg_steps(const std::vector<BatchSize>& probs) {
     return best;
 }
 
-void launch_batch_tiles(bool force, int neighths, int H, hipStream_t s, const BProb2D* pr, const BState* st, int np,
+void launch_batch_tiles(bool force, int ntiles, int H, hipStream_t s, const BProb2D* pr, const BState* st, int np,
                         double sgn, int amode) {
-    if (neighths <= 0) return;
-    const dim3 grid((unsigned)(neighths * kXcds));
+    if (ntiles <= 0) return;
+    const dim3 grid((unsigned)ntiles);
     if (force)
         hipLaunchKernelGGL(batch_tile2d_kernel<true>, grid, dim3(64 * BNW), 0, s, pr, st, np, H, sgn, amode);
     else

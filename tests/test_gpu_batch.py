@@ -307,3 +307,27 @@ def test_fp64_first_then_fp32_reaches_the_fp64_solution(E):
     _say("single context fp64 then fp32", info)
     assert info["relres_fp64"] <= 1e-8 and 0 < info["fp64_iters"] < info["iters"]
     assert _rel(vs.cpu().numpy(), v64[0].cpu().numpy()) <= 2e-8 * conds[0]
+
+
+def _small(k, nx, ny, seed):
+    rng = np.random.default_rng(seed)
+    shape = (ny + 1, nx + 1)
+    mu = np.exp(0.2 * rng.standard_normal(shape))
+    return inputs.Case(f"s{k}", 2, (nx, ny), 4.0 + 0.5 * (k % 7), np.exp(0.2 * rng.standard_normal(shape)), 2 * mu, mu,
+                       rng.standard_normal((2,) + shape), inputs.BC_FREE_TOP_2D)
+
+
+def test_batch_of_many_small_problems(E):
+    """Problems of one tile and of 7 to 17 (whole eighths, one more, one less, as
+    the tiles are dealt to the XCDs in eighths), some of which finish early:
+    the single-problem path's iterates."""
+    sizes = [(5 + k % 9, 4 + k % 13) for k in range(40)] + [(45 * k - 3, 20) for k in (7, 8, 9, 15, 16, 17)]
+    cases = [_small(k, nx, ny, 900 + k) for k, (nx, ny) in enumerate(sizes)]
+    vs, infos, _ = E.Batch(cases).solve([c.f for c in cases], tol=1e-6, maxit=12)
+    for c, v, info in zip(cases, vs, infos):
+        ctx = E.context_from_case(c, autotune=0)
+        w, single = ctx.solve(c.f, tol=1e-6, maxit=12, raise_on_fail=False)
+        assert abs(single["iters"] - info["iters"]) <= 1, (c.n, single, info)
+        if single["iters"] == info["iters"] and single["cr_iters"] == info["cr_iters"] == 0:
+            assert _rel(v.cpu().numpy(), w.cpu().numpy()) <= 1e-9, c.n
+        ctx.close()
