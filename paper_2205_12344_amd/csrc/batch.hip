@@ -85,16 +85,19 @@ thread_local std::string g_batch_err;
         if (s_ != ELWH_OK) return s_; \
     } while (0)
 
-// Steps per register-tile tick for the problems of live (null: all).
-int reg_steps(const elwh_batch* b, const std::vector<BState>* live) {
+// Interior sizes of the problems of live (null: all).
+std::vector<BatchSize> sizes(const elwh_batch* b, const std::vector<BState>* live) {
     std::vector<BatchSize> v;
     for (int p = 0; p < b->np; ++p) {
         const elwh_ctx* c = b->ctx[p];
         if (!live || (*live)[p].active)
             v.push_back(BatchSize{c->L.nx, c->mr.hi - c->mr.lo + 1, c->plan.nt * c->opts.periods});
     }
-    return batch_reg_steps(v);
+    return v;
 }
+
+// Steps per register-tile tick for them.
+int reg_steps(const elwh_batch* b, const std::vector<BState>* live) { return batch_reg_steps(sizes(b, live)); }
 
 // Descriptors of every problem for one phase (precision fp32), vector roles
 // given by indices into the context's work vectors.
@@ -566,10 +569,12 @@ elwh_status elwh_batch_create(int nprob, const elwh_grid* grids, const double* c
     b->h_st.assign(nprob, BState{});
     b->info.assign(nprob, elwh_info{});
     // untuned tiles: supported by the single-step and the kb-step batch kernels
-    const Tile t0 = batch_kb(o.fuse) == 4 ? Tile{1, 10} : Tile{2, 8};   // (FP64 at 4: register tiles instead)
+    const Tile t0 = batch_kb(o.fuse) == 4 ? Tile{1, 10} : Tile{2, 8};
     b->tile[0] = t0;
     b->tile[1] = t0;
-    b->reg = batch_kb(o.fuse) == 4;   // (fewer steps per tick asked for: the marching kernels)
+    // (fewer steps per tick asked for, or mostly strips: the marching kernels)
+    const std::vector<BatchSize> all = sizes(b, nullptr);
+    b->reg = batch_kb(o.fuse) == 4 && !batch_strips(all.data(), nprob);
     if (o.autotune) {
         // (register-tile ticks choose their steps from the sizes)
         if (!b->reg && autotune_batch(b, false) != ELWH_OK) return fail(ELWH_ERR_HIP, b->err);

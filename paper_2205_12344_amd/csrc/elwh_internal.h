@@ -408,6 +408,7 @@ struct BatchSize {
 };
 int batch_reg_tiles(int nx, int nrows, int H, int* ntx);
 int batch_reg_steps(const std::vector<BatchSize>& probs);
+bool batch_strips(const BatchSize* probs, int n);
 void launch_batch_tiles(bool force, int ntiles, int H, hipStream_t s, const BProb2D* pr, const BState* st, int np,
                         double sgn, int amode);
 int batch_cols(int V);

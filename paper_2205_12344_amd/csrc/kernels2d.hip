@@ -390,8 +390,8 @@ void launch_batch_step(bool fp32, int V, int TY, bool force, bool comp, int nblo
         ELWH_BT(float, 1, 4) ELWH_BT(float, 1, 8) ELWH_BT(float, 1, 10) ELWH_BT(float, 2, 4) ELWH_BT(float, 2, 8)
         ELWH_BT(float, 2, 16) ELWH_BT(float, 4, 8)
     } else {
-        ELWH_BT(double, 1, 4) ELWH_BT(double, 1, 8) ELWH_BT(double, 2, 4) ELWH_BT(double, 2, 8)
-        ELWH_BT(double, 2, 16)
+        ELWH_BT(double, 1, 4) ELWH_BT(double, 1, 8) ELWH_BT(double, 1, 10) ELWH_BT(double, 2, 4)
+        ELWH_BT(double, 2, 8) ELWH_BT(double, 2, 16)
     }
 #undef ELWH_BT
 }

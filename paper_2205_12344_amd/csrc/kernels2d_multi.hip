@@ -580,6 +580,7 @@ void launch_batch_multi(bool fp32, int V, int TY, int kb, bool force, bool comp,
     } else {
         ELWH_BMT(double, 1, 4, 2) ELWH_BMT(double, 1, 8, 2) ELWH_BMT(double, 2, 4, 2) ELWH_BMT(double, 2, 8, 2)
         ELWH_BMT(double, 2, 16, 2)
+        ELWH_BMT(double, 1, 4, 4) ELWH_BMT(double, 1, 8, 4) ELWH_BMT(double, 1, 10, 4)
     }
 #undef ELWH_BMT
 }

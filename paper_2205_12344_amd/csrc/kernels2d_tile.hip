@@ -591,6 +591,27 @@ int batch_reg_tiles(int nx, int nrows, int H, int* ntx) {
     return *ntx * tiles_y(nrows, BNW * BR, H);
 }
 
+// Whether wide problems of a few rows carry the batch: as for one problem
+// (strip2d_rule), a tile's other rows are empty and the marching ticks are faster.
+// ms for four iterations of 30 steps, tiles against marching ticks: 4 problems of
+// 10000 x 3 0.37 / 0.33, 4 of 100000 x 3 (15 steps) 1.72 / 0.85, 48 of 1000 x 3 2.47 / 2.25,
+// 4 of 20000 x 8 0.57 / 0.54, 4 of 40000 x 8 0.90 / 0.74; 16 of 2000 x 3 0.47 / 0.48, 400 of
+// 60 x 8 9.92 / 9.98, 4 of 40000 x 12 0.98 / 1.25; with 4 problems of 512^2, one of
+// 100000 x 3 1.03 / 1.10, four 2.26 / 1.90.
+bool batch_strips(const BatchSize* probs, int n) {
+    int64_t narrow = 0, wide = 0, strips = 0, tiles = 0;
+    for (int p = 0; p < n; ++p) {
+        const BatchSize& q = probs[p];
+        int ntx;
+        const int64_t t = batch_reg_tiles(q.nx, q.nrows, 4, &ntx);
+        tiles += t;
+        if (q.nrows > 8) continue;
+        strips += t;
+        (q.nrows <= 4 ? narrow : wide) += q.nx;
+    }
+    return (narrow > 36000 || narrow + wide > 70000) && 4 * strips > 3 * tiles;
+}
+
 // Steps per tick for problems of the given interior sizes and steps per
 // application, from the model above: every tick costs its launches (25 us with
 // the counters and the CG kernels) and its rounds of tiles; the longest

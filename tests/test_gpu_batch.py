@@ -331,3 +331,20 @@ def test_batch_of_many_small_problems(E):
         if single["iters"] == info["iters"] and single["cr_iters"] == info["cr_iters"] == 0:
             assert _rel(v.cpu().numpy(), w.cpu().numpy()) <= 1e-9, c.n
         ctx.close()
+
+
+def test_batch_of_strips(E):
+    """Problems of a few rows and many columns take the marching ticks: the
+    single-problem path's iterates after three iterations."""
+    cases = [_small(k, nx, ny, 950 + k) for k, (nx, ny) in enumerate([(13000, 3), (14001, 2), (12500, 4)])]
+    for c in cases:
+        c.length = (c.n[0] / 100, c.n[1] / 100)
+        op = Operator(Problem(2, c.n, length=c.length, bc=c.bc), c.rho, c.lam, c.mu)
+        c.omega = 2 * np.pi / (13 * 0.8 * 2 / np.sqrt(op.gershgorin())) * 1.001      # the rule's N_T is 13
+    vs, infos, st = E.Batch(cases, nt=13).solve([c.f for c in cases], tol=0.0, maxit=3)
+    assert st == "OK" and all(i["iters"] == 3 for i in infos)
+    for c, v in zip(cases, vs):
+        ctx = E.context_from_case(c, nt=13, autotune=0)
+        w, _ = ctx.solve(c.f, tol=0.0, maxit=3, raise_on_fail=False)
+        assert _rel(v.cpu().numpy(), w.cpu().numpy()) <= 1e-9, c.n
+        ctx.close()

@@ -77,3 +77,19 @@ def test_march3d(rule, nx, ny, np, march, tiling):
 def test_march3d_against_single_step_tilings(rule, nx, ny, np, march, tiling):
     r = rule("_ZN4elwh12march3d_ruleEiiib", I, I, I, B, restype=I)
     assert (r(nx, ny, np, False) >= 2) == (march < tiling)
+
+
+class _BatchSize(ctypes.Structure):
+    _fields_ = [("nx", I), ("nrows", I), ("nsteps", I)]
+
+
+# (problems, whether the marching ticks were the faster ones)
+@pytest.mark.parametrize("probs,march", [
+    ([(10000, 3)] * 4, True), ([(100000, 3)] * 4, True), ([(1000, 3)] * 48, True), ([(20000, 8)] * 4, True),
+    ([(40000, 8)] * 4, True), ([(100000, 3)] * 4 + [(512, 512)] * 4, True), ([(40000, 3)] * 2 + [(256, 256)], True),
+    ([(2000, 3)] * 16, False), ([(60, 8)] * 400, False), ([(40000, 12)] * 4, False), ([(3000, 16)] * 48, False),
+    ([(100000, 3)] + [(512, 512)] * 4, False), ([(1024, 1024)] * 16, False), ([(30, 30)] * 1000, False),
+])
+def test_batch_strips(rule, probs, march):
+    strips = rule("_ZN4elwh12batch_stripsEPKNS_9BatchSizeEi", ctypes.POINTER(_BatchSize), I)
+    assert strips((_BatchSize * len(probs))(*[(nx, rows, 30) for nx, rows in probs]), len(probs)) == march
