@@ -510,7 +510,7 @@ elwh_status elwh_autotune(elwh_ctx* ctx, int prec, int reps, double* best_step_u
  * all differ), solved together: each batched step ("tick") advances every
  * unfinished problem by several steps of its own filter application in one
  * launch: FP64 with opts->fuse >= 4 by up to 4 to 10 (one count for the batch,
- * from its sizes), otherwise by opts->fuse >= 4 ? 4 : 2 where that many are
+ * from its sizes) unless wide problems of a few rows carry it, otherwise by opts->fuse >= 4 ? 4 : 2 where that many are
  * left and by one step where not (always for opts->fuse = 1), in one
  * multi-step and one single-step launch over
  * all problems; a problem whose application ends runs its CG update on the
@@ -525,7 +525,7 @@ elwh_status elwh_autotune(elwh_ctx* ctx, int prec, int reps, double* best_step_u
  *   (DEVICE pointers, copied), omega[i], bc[6*i .. 6*i+5]; opts shared
  *   (opts->stream is the caller's stream; the batch works on its own stream
  *   and orders itself after / before the caller's stream).  Picks the batch
- *   tiling by timing when opts->autotune.  Errors: ELWH_ERR_ARG (also for a
+ *   tiling by timing when opts->autotune (register-tile ticks have none).  Errors: ELWH_ERR_ARG (also for a
  *   3-D problem), ELWH_ERR_ALLOC, ELWH_ERR_HIP.
  * elwh_batch_solve (with ELWH_PROGRESS=1 in the environment it prints a progress
  *   line to stderr at most every 10 s): f[i], x0[i] (x0 or any x0[i] may be NULL: zero guess),
@@ -533,7 +533,9 @@ elwh_status elwh_autotune(elwh_ctx* ctx, int prec, int reps, double* best_step_u
  *   in elwh_solve; infos (nullable) receives nprob records.  Synchronous.
  *   Returns ELWH_OK when every problem converged, else the first failure.
  * elwh_batch_stats: wall seconds of the last solve, number of batched steps
- *   (ticks), and the FP64 / FP32 tilings {vec, rows}.
+ *   (ticks), and the FP64 / FP32 tilings {vec, rows}; where FP64 phases take
+ *   register-tile ticks (opts->fuse >= 4 and not mostly wide problems of a few
+ *   rows) tile64 is {0, steps per tick while every problem is active}.
  */
 typedef struct elwh_batch elwh_batch;
 elwh_status elwh_batch_create(int nprob, const elwh_grid* grids, const double* const* rho,

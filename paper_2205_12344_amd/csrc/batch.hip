@@ -610,9 +610,9 @@ elwh_status elwh_batch_stats(const elwh_batch* b, double* seconds, long long* ti
     if (!b) return ELWH_ERR_ARG;
     if (seconds) *seconds = b->seconds;
     if (ticks) *ticks = b->ticks;
-    if (tile64) {
-        tile64[0] = b->tile[0].V;
-        tile64[1] = b->tile[0].TY;
+    if (tile64) {   // (register-tile ticks have no such tiling: their steps)
+        tile64[0] = b->reg ? 0 : b->tile[0].V;
+        tile64[1] = b->reg ? reg_steps(b, nullptr) : b->tile[0].TY;
     }
     if (tile32) {
         tile32[0] = b->tile[1].V;

@@ -584,6 +584,7 @@ class Batch:
         return vs, [infos[k].as_dict() for k in range(self.n)], STATUS_NAMES[st]
 
     def stats(self):
+        """Of the last solve; tile64 is {0, steps per tick} where FP64 phases take register tiles."""
         sec = ctypes.c_double()
         ticks = ctypes.c_longlong()
         t64 = (ctypes.c_int * 2)()

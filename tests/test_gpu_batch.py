@@ -348,3 +348,12 @@ def test_batch_of_strips(E):
         w, _ = ctx.solve(c.f, tol=0.0, maxit=3, raise_on_fail=False)
         assert _rel(v.cpu().numpy(), w.cpu().numpy()) <= 1e-9, c.n
         ctx.close()
+
+
+def test_batch_stats_name_what_runs(E):
+    """tile64: the steps per register-tile tick, or the marching ticks' tiling."""
+    cases = _cases()[:3]
+    v, steps = E.Batch(cases).stats()["tile64"]
+    assert v == 0 and 4 <= steps <= 10
+    v, rows = E.Batch(cases, fuse=2).stats()["tile64"]
+    assert v in (1, 2) and rows in (4, 8, 16)
