@@ -2,17 +2,17 @@
 
 A step is one Krylov iteration of the solve on the 2-D 1024 x 1024 random
 log-normal medium with a traction-free top (FP64): one A_h = I - S_h
-application (the half-step launch and the fused launches of K = 4 time
-steps each, plus one shorter launch when 4 does not divide N_T - 1, over
-every unknown node, each step with its trapezoid accumulation)
+application (ceil(N_T / H) register-tile launches of up to H time steps each,
+the start included, over every unknown node, each step with its trapezoid
+accumulation)
 plus the FP64 M-inner-product reductions and the CG vector updates.  Inputs are resident
 in HBM before timing.  value = lattice updates per second, one lattice
 update = one unknown node advanced one time step (both components), with its
 accumulation.
 
-The JSON line also carries the roofline of the fused K-step kernel (HIP-event
-durations of its launches on the same workload and tiling, with N_T rounded
-so that every launch takes K steps), the HBM ceiling a STREAM triad reaches, the FP32-stepping and
+The JSON line also carries the roofline of the fused H-step kernel (HIP-event
+durations of its launches on the same workload and tile shape, with N_T rounded
+so that every launch takes H steps), the HBM ceiling a STREAM triad reaches, the FP32-stepping and
 single-step variants, the step kernels of the 3-D cube, of mapped 2-D and 3-D
 grids and of the two-field operator, the time to residual 1e-8 of the
 benchmark problem and of a 3-D cube, the 48-problem ragged batch, the
@@ -849,7 +849,7 @@ def main():
     # the start included; each reads u^n, u^{n-1}, the accumulator and the three
     # coefficients once and writes two levels and the accumulator (the first has no
     # u^{n-1} to read)
-    napp = prof["nstep"] // max(nt - 1, 1)
+    napp = prof["ninit"]
     fuse = elwh.default_opts().fuse
     nrows = nodes // (case.n[0] - 1)
     nw, nr, h = register_tile(case.n[0], nrows, nt)
@@ -863,7 +863,7 @@ def main():
     ck = elwh.context_from_case(case, nt=nt_k, autotune=0)
     pk = kernel_rate(ck, 10)
     ck.close()
-    launches = pk["nstep"] // (nt_k - 1) * -(-nt_k // h)
+    launches = pk["ninit"] * -(-nt_k // h)
     step_avg_ms = pk["step_ms"] / max(launches, 1)
     achieved = bytes_launch / (step_avg_ms * 1e-3) / 1e9
     traffic = read_traffic("tile2d_f64_square1024", (nw * nr, h), "2dtile")
@@ -909,7 +909,7 @@ def main():
         c2 = elwh.context_from_case(case, **kw)
         p = kernel_rate(c2, 10)
         t2 = c2.get_tile(elwh.FP64 if prec == "f64" else elwh.FP32_STEP)
-        napp = p["nstep"] // max(nt - 1, 1)
+        napp = p["ninit"]
         bapp, lapp = phase_bytes(2, prec, fuse_v, nt, nodes)
         gbs = bapp * napp / (p["step_ms"] * 1e-3) / 1e9
         variants[tag] = {"tile": list(t2), "steps_per_launch": fuse_v,
@@ -931,7 +931,7 @@ def main():
     nt4k = ctx4k.info()["nt"]
     p = kernel_rate(ctx4k, 3)
     t4k = ctx4k.get_tile(elwh.FP64)
-    napp = p["nstep"] // max(nt4k - 1, 1)
+    napp = p["ninit"]
     bapp, lapp = phase_bytes(2, "f64", fuse, nt4k, n4k)
     gbs = bapp * napp / (p["step_ms"] * 1e-3) / 1e9
     variants["f64_square4096"] = {

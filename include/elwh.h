@@ -459,12 +459,15 @@ elwh_status elwh_dot_M_noalloc(const elwh_grid* grid, const double* rho, const i
 elwh_status elwh_stream_triad(double* a, const double* b, const double* c, double s, long long n, void* stream);
 
 /*
- * Kernel timing for measurement.  While enabled, every fused-step launch of
- * the filter (Sec. 4.3 step + trapezoid accumulation; the half-step launch
- * is counted separately) is bracketed by a pair of HIP events on the
- * context's stream.  elwh_profile_read synchronises the stream and returns
- * the summed kernel time in milliseconds and the launch counts since the
- * last read or enable, then resets them.  Enabling also resets.
+ * Kernel timing for measurement.  While enabled, every filter application
+ * (Sec. 4.3 steps + trapezoid accumulation) is timed by HIP events on the
+ * context's stream: its half step and the time steps that follow, or, where
+ * register tiles take the half step in their first launch, all its time steps
+ * together.  elwh_profile_read synchronises the stream and returns the summed
+ * kernel time of the steps in milliseconds and their number (steps, not
+ * launches; step_ms / nstep is the time of one), the time of the half steps timed
+ * apart, and the number of applications since the last read or enable, then
+ * resets them.  Enabling also resets.
  * Errors: ELWH_ERR_ARG (NULL ctx), ELWH_ERR_HIP.
  */
 elwh_status elwh_profile_enable(elwh_ctx* ctx, int on);

@@ -207,7 +207,7 @@ struct elwh_ctx {
     // half step, after the last step) on the context's stream
     bool prof_on = false;
     std::vector<hipEvent_t> prof_ev;   // pool, reused
-    std::vector<int> prof_nsteps;      // step launches per recorded application
+    std::vector<int> prof_nsteps;      // time steps of its last part, per recorded application
     size_t prof_used = 0;              // applications recorded since the last read
 
     // impedance y faces (two-field path): flags, damping rows g (4 x P: u and v

@@ -322,7 +322,7 @@ void run_filter_curv_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bo
         prev = A.steps > 1 ? o[0] : cur;
         cur = o[1];
     }
-    prof_mark(c, 2, nsteps - 1);
+    prof_mark(c, 2, nsteps);
 }
 
 }  // namespace elwh

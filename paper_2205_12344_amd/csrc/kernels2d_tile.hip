@@ -486,7 +486,7 @@ void run_filter_tile2d(elwh_ctx* c, const TileShape& t, const double* x, bool wi
         prev = A.steps > 1 ? o[0] : cur;
         cur = o[1];
     }
-    prof_mark(c, 2, nsteps - 1);
+    prof_mark(c, 2, nsteps);
 }
 
 void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x0, const double* z1, bool with_force,
@@ -525,7 +525,7 @@ void run_filter_twofield_tile2d(elwh_ctx* c, const TileShape& t, const double* x
         prev = A.steps > 1 ? o[0] : cur;
         cur = o[1];
     }
-    prof_mark(c, 2, N);
+    prof_mark(c, 2, N + 1);
 }
 
 // ===========================================================================
