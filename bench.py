@@ -25,6 +25,7 @@ Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--budget S] [--no-cp
 """
 
 import argparse
+import ctypes
 import json
 import math
 import os
@@ -98,21 +99,19 @@ def phase_bytes(dim, tag, fuse, nt, nodes):
     return b, len(ks)
 
 
+class _TileShape(ctypes.Structure):
+    _fields_ = [("NW", ctypes.c_int), ("R", ctypes.c_int), ("H", ctypes.c_int)]
+
+
 def register_tile(nx, nrows, nsteps):
-    """The library's register tiles for FP64 steps of a 2-D Cartesian grid
-    (tile2d_pick in kernels2d_tile.hip): (wavefronts, rows each, steps per
-    launch), by the same model of an application's time."""
-    best = None
-    for nw, r in ((4, 4), (8, 3), (8, 4)):
-        rows = nw * r
-        for h in range(3, min(12, rows // 2 - 1) + 1):
-            tiles = -(-(nx - 1) // (64 - 2 * h)) * -(-nrows // (rows - 2 * h))
-            rounds, inner = -(-tiles // 256), (64 - 2 * h) * (rows - 2 * h)
-            t = (-(-nsteps // h) * (1.5 + rounds * (3.0 + 0.04 * rows + 2.4e-3 * inner))
-                 + rounds * nsteps * (0.11 + 0.018 * rows))
-            if best is None or t < best[0]:
-                best = (t, nw, r, h)
-    return best[1:]
+    """The library's register tiles for FP64 steps of a 2-D Cartesian grid:
+    (wavefronts, rows each, steps per launch), from the library itself
+    (elwh::tile2d_pick of kernels2d_tile.hip, by its linker name)."""
+    from paper_2205_12344_amd import elwh
+    pick = elwh.lib._ZN4elwh11tile2d_pickEiiib
+    pick.argtypes, pick.restype = [ctypes.c_int] * 3 + [ctypes.c_bool], _TileShape
+    t = pick(nx, nrows, nsteps, False)
+    return t.NW, t.R, t.H
 
 
 def log(*a):

@@ -58,3 +58,11 @@ def test_more_than_one_gpu_is_refused():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr
+
+
+@pytest.mark.parametrize("nx,nrows,nt", [(1024, 1024, 63), (64, 64, 141), (611, 373, 90), (2, 2, 3)])
+def test_register_tile_is_the_librarys(nx, nrows, nt):
+    """Wavefronts, rows and steps per launch come from the library: a shape its
+    kernels are built for, with inner rows left."""
+    nw, r, h = bench.register_tile(nx, nrows, nt)
+    assert (nw, r) in ((4, 4), (8, 3), (8, 4)) and 3 <= h <= min(12, nw * r // 2 - 1)
