@@ -423,7 +423,7 @@ def time_to_tol(elwh, case, tol=1e-8, maxit=20000, **kw):
     ctx.close()
     return {"seconds": round(el, 3), "iters": info["iters"], "status": info["status"],
             "relres_fp64": info["relres_fp64"], "outer": info["outer"], "fp64_iters": info["fp64_iters"],
-            "nt": info["nt"]}
+            "cr_iters": info["cr_iters"], "napply": info["napply"], "nt": info["nt"]}
 
 
 def sequential_plain(elwh, first_seed=4096, n=48, tol=1e-8, maxit=4000):
