@@ -222,3 +222,29 @@ def test_convolution_tiles(E, monkeypatch, B, H, W):
             a, b = g[off:off + n], gr[off:off + n]
             assert np.linalg.norm(a - b) <= 2e-2 * np.linalg.norm(b), (k, n)
             off += n
+
+
+def test_weight_gradient_of_several_tiles_per_workgroup(E, monkeypatch):
+    """9 samples of 112 x 144: more pixel tiles than shares of the weight gradient
+    in every kind of layer (one, several of 32 x 32 channels, the first, the
+    concatenated ones), so workgroups walk two to four tiles, the last share
+    fewer.  The bar per layer is test_convolution_tiles'."""
+    B, H, W = 9, 112, 144
+    rng = np.random.default_rng(77)
+    theta = _setup(12, 1, 16)[0]
+    x = rng.standard_normal((B, H, W, 7)).astype(np.float32)
+    y = rng.standard_normal((B, H, W, 2)).astype(np.float32)
+    w = rng.uniform(0.5, 1.5, (B, H, W)).astype(np.float32)
+    im2col, unpack = unet.im2col, unet.unpack
+    monkeypatch.setattr(unet, "im2col", lambda X: _bf16(im2col(X)))
+    monkeypatch.setattr(unet, "unpack", lambda t: [(_bf16(Wl), b) for Wl, b in unpack(t)])
+    _, gr, _ = unet.loss_and_grad(theta, x.astype(np.float64), y.astype(np.float64), w.astype(np.float64))
+    net = E.WarmStartNet(B, H, W)
+    net.set_params(theta)
+    _, g = net.loss_grad(_t(x), _t(y), _t(w))
+    off = 0
+    for k, (ci, co, _) in enumerate(unet.LAYERS):
+        for n in (9 * ci * co, co):
+            a, b = g[off:off + n], gr[off:off + n]
+            assert np.linalg.norm(a - b) <= 2e-2 * np.linalg.norm(b), (k, n)
+            off += n
