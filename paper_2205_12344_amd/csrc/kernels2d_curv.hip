@@ -36,6 +36,10 @@
 //     D+q(Kbar^qq D-q U) - (K^rr_C + K^rr_S)(U_C - U_S) / h_r^2
 //     + [P'_{i+1} - P'_{i-1} - (Q_C + Q_S)] / (2 h_q h_r),
 // P' = K^qr (U_C - U_S), and the bottom side mirrors it.
+//
+// FP32 steps run it, and in FP64 wide grids of a few rows (strip2d_rule: 100000 x 2 380
+// us for 60 steps, register tiles 912) and a tiling that was asked for; elsewhere FP64
+// takes register tiles (kernels2d_curv_tile.hip), 2 to 4 times faster.
 #include "step2d_common.h"
 
 namespace elwh {

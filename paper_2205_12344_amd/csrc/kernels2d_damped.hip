@@ -27,6 +27,11 @@
 // 64-lane wavefront per x-strip of 64 V columns, TY rows marched upward with
 // the three stencil rows in registers and the next row's loads issued one
 // iteration ahead.
+//
+// What still runs it: fewer steps per launch asked for (fuse < 4), wide grids of a few
+// rows (strip2d_rule: 100000 x 2 297 us for 61 steps, register tiles 772), a tiling that
+// was asked for.  Elsewhere register tiles (kernels2d_tile.hip) are 1.5 to 3 times
+// faster.
 #include "step2d_common.h"
 
 namespace elwh {

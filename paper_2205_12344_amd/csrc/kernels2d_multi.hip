@@ -25,6 +25,10 @@
 // stage K has added its term, so the accumulation order per node is that of
 // K single steps.  The two output levels go to buffers other than the inputs:
 // a node's u^{n-1} and u^n are read by the blocks on both sides of it.
+//
+// FP32 steps run it, and in FP64 more than about 2000^2 nodes, wide grids of a few rows
+// (100000 x 3 252 us for 60 steps, register tiles 319), batches of those, fuse < 4 and a
+// tiling that was asked for; elsewhere FP64 takes register tiles (kernels2d_tile.hip).
 #include <type_traits>
 
 #include "step2d_common.h"

@@ -20,6 +20,9 @@
 // updates, against 144 per update.  The
 // accumulation order per node (w_{n+1} u^{n+1}, then w_{n+2} u^{n+2}) is that
 // of two single steps.
+//
+// FP32 steps run it, and in FP64 thin grids and a tiling that was asked for
+// (march3d_rule; 200 x 200 x 3 164 us for 20 steps, march 189).
 #include "elwh_internal.h"
 #include "lanes.h"
 #include "step3d_common.h"

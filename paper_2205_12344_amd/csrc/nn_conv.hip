@@ -23,7 +23,9 @@
 //
 // Sums run over taps, then channels in steps of 16, by v_mfma_f32_32x32x16_bf16
 // (and, for the input gradient, per tap from zero and then over the taps), the
-// order of the im2col GEMMs this replaced, so the results are the same bits.
+// order of the im2col GEMMs these replaced: the forward pass and the input
+// gradient of given operands are the same bits.  Weight and bias gradients sum over
+// pixels, in another order (FP32 as before; 3e-7 apart at 16 samples of 256^2).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
