@@ -156,6 +156,7 @@ KERNEL_SOURCES = {
     "2d": ("kernels2d.hip", "kernels2d_multi.hip", "step2d_common.h", "xcd.h", "lanes.h"),
     "2dtile": ("kernels2d_tile.hip", "step2d_common.h", "xcd.h", "lanes.h"),
     "3d": ("kernels3d.hip", "kernels3d_k2.hip", "step3d_common.h", "xcd.h", "lanes.h"),
+    "3dmarch": ("kernels3d_march.hip", "step3d_common.h", "xcd.h", "lanes.h"),
 }
 
 
@@ -684,7 +685,8 @@ def counters_pass_3d(rb, tz, prec):
     """Dispatches for the HBM-traffic counters of the 3-D step kernels: the
     256 MiB calibration copy, then two A_h applications of the 256^3
     layered-cube workload with the fixed tiling (RB, TZ) (RB 2, 4, 6: two
-    steps per launch; RB 1: single steps), FP64 or FP32 compensated."""
+    steps per launch; RB 1: single steps; 0, 0: the FP64 march), FP64 or FP32
+    compensated."""
     import torch
     from paper_2205_12344_amd import elwh, inputs
     x = torch.ones(2 ** 25, dtype=torch.float64, device="cuda")
@@ -693,7 +695,8 @@ def counters_pass_3d(rb, tz, prec):
     torch.cuda.synchronize()
     kw = {} if prec == "f64" else {"prec": elwh.FP32_STEP, "compensated": 1}
     ctx = elwh.context_from_case(inputs.layered_cube(), autotune=0, **kw)
-    ctx.set_tile(elwh.FP64 if prec == "f64" else elwh.FP32_STEP, int(rb), int(tz))
+    if int(rb) > 0:
+        ctx.set_tile(elwh.FP64 if prec == "f64" else elwh.FP32_STEP, int(rb), int(tz))
     z = torch.zeros(ctx.field_shape, dtype=torch.float64, device="cuda")
     for _ in range(2):
         ctx.apply_A(z)
@@ -770,7 +773,7 @@ def main():
     ap.add_argument("--counters-mapped", default=None, metavar="V,TY",
                     help="the same for the mapped-grid workload")
     ap.add_argument("--counters-3d", default=None, metavar="RB,TZ,PREC",
-                    help="the same for the 256^3 layered cube (PREC f64 or f32c; RB 1 = single steps)")
+                    help="the same for the 256^3 layered cube (PREC f64 or f32c; RB 1 = single steps, 0,0,f64 = the march)")
     ap.add_argument("--counters-twofield", default=None, metavar="V,TY",
                     help="the same for the two-field (impedance) workload")
     ap.add_argument("--twofield-only", action="store_true",
@@ -977,7 +980,9 @@ def main():
                              # both precisions, so that FP64 and FP32 compare
                              "effective_frac": round(BYTES_PER_LUP[(3, "f64", 1)] * n3 / step_us / 1e3
                                                      / HBM_PEAK_GBS, 4),
-                             "traffic": read_traffic(f"step3d_{tag}_cube256", (rb, tz), "3d")}
+                             # (the march has no tiling)
+                             "traffic": (read_traffic("march3d_f64_cube256", (0, 0), "3dmarch") if tag == "f64"
+                                         else read_traffic(f"step3d_{tag}_cube256", (rb, tz), "3d"))}
             log(f"3d {tag} fuse {fuse3}: tile {rb},{tz}, {step_us:.1f} us per step, {gbs:.0f} GB/s")
             ctx3.close()
     del c3

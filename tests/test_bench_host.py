@@ -66,3 +66,28 @@ def test_register_tile_is_the_librarys(nx, nrows, nt):
     kernels are built for, with inner rows left."""
     nw, r, h = bench.register_tile(nx, nrows, nt)
     assert (nw, r) in ((4, 4), (8, 3), (8, 4)) and 3 <= h <= min(12, nw * r // 2 - 1)
+
+
+def test_traffic_is_read_for_the_kernel_that_runs(tmp_path, monkeypatch):
+    """Counters count for the tiling and for the kernel sources they were taken with."""
+    (tmp_path / "profiles").mkdir()
+    csrc = tmp_path / "paper_2205_12344_amd" / "csrc"
+    csrc.mkdir(parents=True)
+    for family in bench.KERNEL_SOURCES:
+        for f in bench.KERNEL_SOURCES[family]:
+            (csrc / f).write_text(f)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    (tmp_path / "profiles" / "march3d_f64_cube256_counters.txt").write_text(
+        f"kernel_source_hash: {bench.kernel_source_hash('3dmarch')}\ntraffic_bytes_per_launch[0,0]: 123\n")
+    assert bench.read_traffic("march3d_f64_cube256", (0, 0), "3dmarch") == 123.0
+    assert bench.read_traffic("march3d_f64_cube256", (6, 32), "3dmarch") is None
+    (csrc / "kernels3d_k2.hip").write_text("changed")
+    assert bench.read_traffic("march3d_f64_cube256", (0, 0), "3dmarch") == 123.0
+    (csrc / "kernels3d_march.hip").write_text("changed")
+    assert bench.read_traffic("march3d_f64_cube256", (0, 0), "3dmarch") is None
+
+
+def test_kernel_sources_exist():
+    for files in bench.KERNEL_SOURCES.values():
+        for f in files:
+            assert os.path.exists(os.path.join(ROOT, "paper_2205_12344_amd", "csrc", f)), f
