@@ -500,8 +500,8 @@ elwh_status elwh_profile_read(elwh_ctx* ctx, double* step_ms, int* nstep, double
  * variable ELWH_TUNE_CACHE names a file, in that file as JSON lines keyed by
  * (arch, dim, precision, accumulator, grid size); a choice found there is taken and
  * best_step_us is -1.  opts.autotune = 1 does the same at create, but times
- * nothing in FP64 where the grid's size decides for the register tiles or the march
- * (a choice made by elwh_autotune before is kept).  Synchronous.
+ * nothing where there is one tiling, or in FP64 where the grid's size decides for the
+ * register tiles or the march (a choice made by elwh_autotune before is kept).  Synchronous.
  * Errors: ELWH_ERR_ARG (unsupported tiling), ELWH_ERR_HIP.
  */
 elwh_status elwh_set_tile(elwh_ctx* ctx, int prec, int vec, int rows);

@@ -660,7 +660,7 @@ elwh_status ctx_solve_fallback(elwh_ctx* c, int method, double tol, int maxit, i
 }  // namespace elwh
 
 namespace {
-bool adopt_own64(elwh_ctx* c);
+bool adopt_choice(elwh_ctx* c, bool fp32);
 // Create a context; xc/yc non-null: a mapped 2-D grid with these node
 // coordinates (host copies are taken here, like the materials).
 elwh_status create_impl(const elwh_grid* grid_in, const double* xc, const double* yc, const double* zc, const double* rho,
@@ -955,10 +955,10 @@ elwh_status create_impl(const elwh_grid* grid_in, const double* xc, const double
         c->tile32 = Tile{1, 16};
     }
     if (o.autotune) {
-        // (nothing is timed where the sizes decide for register tiles or the march)
-        if (!adopt_own64(c) && (st = elwh_autotune(c, ELWH_FP64, 2, nullptr)) != ELWH_OK) return fail(st);
-        if (o.prec == ELWH_FP32_STEP && (st = elwh_autotune(c, ELWH_FP32_STEP, 2, nullptr)) != ELWH_OK)
-            return fail(st);
+        for (const bool fp32 : {false, true}) {
+            if ((fp32 && o.prec != ELWH_FP32_STEP) || adopt_choice(c, fp32)) continue;
+            if ((st = elwh_autotune(c, fp32 ? ELWH_FP32_STEP : ELWH_FP64, 2, nullptr)) != ELWH_OK) return fail(st);
+        }
     }
     *out = c;
     return ELWH_OK;
@@ -1699,18 +1699,20 @@ void take_choice(elwh_ctx* c, bool fp32, const Tile& t) {
     if (step_rule(c) != STEP_TILING) c->own64 = t.V > 0 ? 0 : 1;
 }
 
-// At create: where the sizes alone decide for register tiles or the march, take
-// them, or what elwh_autotune found for such a context, and time nothing.
-bool adopt_own64(elwh_ctx* c) {
-    if (step_rule(c) != STEP_OWN) return false;
-    const TuneKey key = tune_key(c, false);
+// At create, where there is nothing to time: the sizes alone decide for register
+// tiles or the march, or there is one tiling.  A choice that elwh_autotune made
+// for such a context is taken.
+bool adopt_choice(elwh_ctx* c, bool fp32) {
+    const bool one = c->mapped && c->L.dim == 3;
+    if (!one && (fp32 || step_rule(c) != STEP_OWN)) return false;
+    const TuneKey key = tune_key(c, fp32);
     Tile t;
     if (!cached_choice(key, &t)) {
-        t = Tile{0, 0};
+        t = one ? Tile{1, 4} : Tile{0, 0};
         std::lock_guard<std::mutex> g(g_tune_mu);
         g_tune[key] = t;
     }
-    take_choice(c, false, t);
+    take_choice(c, fp32, t);
     return true;
 }
 }  // namespace

@@ -60,6 +60,11 @@ def test_create_times_only_what_may_run(E, tmp_path, monkeypatch):
     assert not _entries(path)
     E.Context(2, (83, 61), *media, 9.0, (0, 0, 0, 1), fuse=2)      # marching kernels: their tilings are timed
     assert [e["variant"] for e in _entries(path)] == [2]
+    q, r, z = (np.arange(k + 1) / k for k in (6, 7, 8))
+    grid = [a + np.zeros((9, 8, 7)) for a in (q[None, None, :], r[None, :, None], z[:, None, None])]
+    one = np.ones((9, 8, 7))
+    mapped = E.MappedContext3(*grid, one, 2 * one, one, 3.0, prec=E.FP32_STEP)     # one tiling
+    assert len(_entries(path)) == 1 and mapped.autotune(E.FP64) == mapped.autotune(E.FP32_STEP) == -1.0
     media, _ = _problem((128, 128, 5), 3)                           # near the line: the march and the tilings are
     E.Context(3, (128, 128, 5), *media, 9.0, (0,) * 6)
     assert [(e["dim"], e["variant"]) for e in _entries(path)] == [(2, 2), (3, 2 | 32)]
