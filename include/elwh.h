@@ -482,8 +482,7 @@ elwh_status elwh_profile_read(elwh_ctx* ctx, double* step_ms, int* nstep, double
  * (1, 2, 4, 8) x (4, 8, 16, 32) for single-step launches (opts.fuse = 1),
  * (2, 4, 6) x (8, 16, 32, 64) for two-step launches (fuse >= 2; the workgroup
  * adds two halo rows), where vec = 1 with rows 4 to 32 makes every step a
- * single-step launch (the FP64 choice on large cubes).  Tilings
- * agree with each other to rounding.  They are those of the kernels which FP32
+ * single-step launch.  Tilings agree with each other to rounding.  They are those of the kernels which FP32
  * stepping uses, and FP64 stepping where opts.fuse < 4 on 2-D Cartesian grids,
  * on very large or thin grids, or for an FP64 tiling that elwh_set_tile asked for;
  * elsewhere FP64 steps take register tiles (2-D) or a march (3-D) that have no
